@@ -10,22 +10,44 @@
 //     the n_i:8 inliers as dense nibbles (zeros at the other positions) in
 //     exactly the operand order, so the B fragment is one 16-byte load per
 //     lane and needs no expansion;
-//   * outliers: v_mfma_i32_32x32x32_i8, exact in int32.  Each lane expands
-//     its two groups' (position, code) half-words into 16 dense bytes; with
-//     2:8 outliers the second plane's half-words scatter into the same bytes
-//     (the two positions of a group differ).
-//     Lane half h covers K [16h, 16h + 16) of the 32-K step for both
-//     operands (the K order inside the instruction is free as long as A and B
-//     agree).
+//   * outliers: the int8 instructions, exact in int32.  In the split-K form
+//     v_mfma_i32_32x32x32_i8: each lane expands its two groups' (position,
+//     code) half-words into 16 dense bytes; with 2:8 outliers the second
+//     plane's half-words scatter into the same bytes (the two positions of a
+//     group differ).  Lane half h covers K [16h, 16h + 16) of the 32-K step
+//     for both operands (the K order inside the instruction is free as long
+//     as A and B agree).
 // The branches accumulate apart (fp32 and int32) and meet in the epilogue.
 //
-// A workgroup of four waves covers four 32-row tiles of W and 32*MS tokens;
-// each wave owns one tile and all MS token sub-tiles.  The workgroup stages
-// each 128-K chunk of both activation tensors in LDS once (double-buffered,
-// one barrier per chunk) for its four waves; each wave streams its tile's
-// weights into registers one chunk ahead.
+// Tiled form: a workgroup covers 4*TN 32-row tiles of W and 32*MS tokens with
+// eight waves, two per SIMD.  Four of them (one per TN tiles) multiply the
+// inliers and four the outliers of the same outputs, so that every wave
+// holds one set of accumulators: the fp32 sums and the int32 sums of a 128 x
+// 64 wave tile together would leave a SIMD one wave, whose vector, LDS and
+// memory instructions then add to its matrix time instead of hiding behind
+// it (128 x 256 outputs at M = 4096, 11008x4096: 282 us with one wave for
+// both branches, 268 with two).  The two sums meet in LDS at the end.
+//
+// The outliers run on v_smfmac_i32_32x32x64_i8 (dual_frag.h): at most two of
+// eight positions are stored, so the 2:4 sparse instruction covers them, 64
+// dense K in the time the dense instruction takes for 32 (measured 7.85 PF
+// against 4.05).  W is the first operand (the sparse one), tokens are the
+// columns.
+//
+// The activations of a 128-K chunk are staged in LDS once per workgroup in
+// three buffers (one barrier per chunk); weights stream into registers a
+// chunk and more ahead.  What bounds it: at 128 x 256 the matrix cores need
+// 1024 cycles per chunk, the LDS reads of the activations 770, the vector
+// memory address unit 1160 (a request of 64 lanes x 16 bytes takes it 17
+// cycles, one of 4 bytes a lane 9, one that touches 32 rows 62), and a chunk
+// takes 2500: MfmaUtil 33%.  LLaMA-7B gate 11008x4096 at M = 4096: 268 us
+// (dense int8 outliers, one wave per SIMD: 390); 4096x4096 at M = 256: 14.5
+// (28).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
+#include "dual_frag.h"
 #include "kernels.h"
 #include "tile_out.h"
 
@@ -35,7 +57,8 @@ namespace {
 constexpr int kDWaves = 4;
 constexpr int kDThreads = kDWaves * 64;
 
-typedef int v4i __attribute__((ext_vector_type(4)));
+using namespace dual;
+
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -50,6 +73,8 @@ struct DualArgs {
   int M, N, K, n_chunks, n_tiles;
   int64_t out_off, scale_off, rows_off;
   bool y_bf16 = false;  // Y as bf16
+  int groups = 1, m_blocks = 1;  // tiled form: the grid is 1-D over (tile group, token block)
+  bool y_vec = false;   // Y 16-byte aligned and N a multiple of 4
 };
 
 __device__ __forceinline__ v4i ld16(__amdgpu_buffer_rsrc_t r, uint32_t v, uint32_t s) {
@@ -97,168 +122,404 @@ __device__ __forceinline__ v4i outlier_bytes_np(const uint32_t (&hw)[NP]) {
   return b;
 }
 
-// LDS rows of one 128-K chunk of activations, padded so that the 16-byte
-// fragment reads of 8 consecutive rows fall on distinct banks.
-constexpr int kRowO = kChunkK + 16;      // int8 codes of A_o: 144 bytes
-constexpr int kRowI = kChunkK / 2 + 16;  // fp4 codes of A_i: 80 bytes
+// Physical 16-byte piece of logical piece p of an LDS row: 128-byte rows of
+// A_o codes (8 pieces) and 64-byte rows of A_i codes (4), XORed with a
+// function of the row so that any aligned group of 8 or 16 rows reads one
+// logical piece from distinct banks (32 or 64 banks of 4 bytes).
+__device__ __forceinline__ int swz_o(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+__device__ __forceinline__ int swz_i(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
 
-template <int MS, int NP>
-__global__ __launch_bounds__(kDThreads, MS >= 4 ? 1 : 2) void dual_mfma_kernel(DualArgs a) {
+// Y[idx .. idx + 3] = v through the resource of out_rows (Y 16-byte aligned and
+// N a multiple of 4, so that the four share a row).
+__device__ __forceinline__ void store_out4(const OutRows& y, uint32_t idx, float4 v) {
+  if (y.bf16) {
+    typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+    const u2v q = {uint32_t(bf16_bits(v.x)) | (uint32_t(bf16_bits(v.y)) << 16),
+                   uint32_t(bf16_bits(v.z)) | (uint32_t(bf16_bits(v.w)) << 16)};
+    __builtin_amdgcn_raw_buffer_store_b64(q, y.r, idx * 2u, 0, 0);
+  } else {
+    const v4i q = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(q, y.r, idx * 4u, 0, 0);
+  }
+}
+
+template <int MS, int TN, int NP, int KG>
+__global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(DualArgs a) {
   constexpr int BM = 32 * MS;
-  // one chunk of the workgroup's activations, two buffers
-  __shared__ __align__(16) uint8_t xo_s[2][BM * kRowO];
-  __shared__ __align__(16) uint8_t xi_s[2][BM * kRowI];
-  __shared__ __align__(16) uint32_t ea_s[2][BM];  // the four e8m0 bytes of a row's chunk
+  // LDS: three chunk buffers of the workgroup's activations (xo_s: codes of
+  // A_o, xi_s: of A_i), then the e8m0 scales of A_i as [chunk & 15][row] (the
+  // four bytes of a row's chunk); the epilogue stages its outputs over them
+  constexpr int kXo = BM * kChunkK, kXi = kXo / 2, kEa = 3 * (kXo + kXi);
+  constexpr int kOutW = TN * kTileN, kOutRow = kOutW + 4;  // staged floats per token, padded
+  constexpr int kOutBytes = kDWaves * BM * kOutRow * 4;
+  constexpr int kGroupBytes = kEa + 16 * BM * 4;  // of one K group's loop
+  // KG = 2: the second K group's accumulators, [role][wave][tile][sub-tile][element][lane]
+  constexpr int kRedBytes = KG == 1 ? 0 : 2 * kDWaves * TN * MS * 16 * 64 * 4;
+  constexpr int kLds = KG * kGroupBytes > kOutBytes + kRedBytes ? KG * kGroupBytes : kOutBytes + kRedBytes;
+  __shared__ __align__(16) uint8_t lds[kLds];
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = int(threadIdx.x) % (2 * kDThreads), lane = tid & 63;  // within the K group
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x) / (2 * kDThreads));
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave8 & 3;
+  uint8_t* const xo_s = lds + kg * kGroupBytes;
+  uint8_t* const xi_s = xo_s + 3 * kXo;
+  uint32_t* const ea_s = reinterpret_cast<uint32_t*>(xo_s + kEa);
   const int col = lane & 31, h = lane >> 5;
-  const int m0 = blockIdx.y * BM;
-  const int t_raw = blockIdx.x * kDWaves + wave;
-  const bool tile_ok = t_raw < a.n_tiles;
-  const int tile = min(t_raw, a.n_tiles - 1);  // a spare wave recomputes the last tile, stores nothing
+  int group, mblock;
+  square_work(blockIdx.x, a.groups, a.m_blocks, group, mblock);
+  const int m0 = mblock * BM;
+  const int t0 = (group * kDWaves + wave) * TN;  // the wave's first tile (tiles past the last read 0)
   const int KC = a.n_chunks, last = KC - 1;
+  // the K group's chunks, cn of them from cb on (a second group's last may
+  // lie past the end: its weights read 0)
+  const int cn = KG == 1 ? KC : (KC + 1) / 2, cb = kg * cn;
   const uint32_t K = uint32_t(a.K);
 
   // activations of the workgroup's rows (rows past M read 0)
   const uint32_t rows = uint32_t(min(a.M - m0, BM));
   const __amdgpu_buffer_rsrc_t xo = buffer_rsrc(a.Xo + size_t(m0) * K, rows * K);
   const __amdgpu_buffer_rsrc_t xi = buffer_rsrc(a.Xi + size_t(m0) * (K / 2), rows * (K / 2));
-  const __amdgpu_buffer_rsrc_t ea = buffer_rsrc(a.Ea + size_t(m0) * (K / 32), rows * (K / 32));
-  // the wave's tile: dense inlier nibbles, outlier half-words, inlier scales
-  const __amdgpu_buffer_rsrc_t wn =
-      buffer_rsrc(a.blob + size_t(tile) * KC * kDualNibBytesPerTC, uint32_t(KC) * kDualNibBytesPerTC);
-  const __amdgpu_buffer_rsrc_t wo = buffer_rsrc(a.blob + a.out_off + size_t(tile) * KC * out_bytes_tc<NP>(),
-                                                uint32_t(KC) * out_bytes_tc<NP>());
-  const __amdgpu_buffer_rsrc_t ws = buffer_rsrc(a.blob + a.scale_off + size_t(tile) * KC * kDualScaleBytesPerTC,
-                                                uint32_t(KC) * kDualScaleBytesPerTC);
+  // (from up to 16 rows before, so that the range holds 16 bytes)
+  const uint32_t eback = uint32_t(min(m0, 16)), ebytes = (rows + eback) * (K / 32);
+  const __amdgpu_buffer_rsrc_t ea = buffer_rsrc(a.Ea + size_t(m0 - int(eback)) * (K / 32), ebytes);
 
-  // ---- activation staging: thread tid moves 16-byte pieces tid + 256 i of
-  //      the chunk (8 per row of A_o, 4 per row of A_i) and, below BM, the
-  //      four scale bytes of row tid
-  constexpr int kPo = BM * 8 / kDThreads;                       // BM * 8 >= 256
-  constexpr int kPi = (BM * 4 + kDThreads - 1) / kDThreads;      // 128 pieces at BM = 32
-  struct XRegs { v4i o[kPo]; v4i i[kPi]; uint32_t e; };
-  auto load_x = [&](int c, XRegs& x) __attribute__((always_inline)) {
-    const uint32_t cs = uint32_t(c);
-#pragma unroll
-    for (int j = 0; j < kPo; ++j) {
-      const int p = tid + j * kDThreads;
-      x.o[j] = ld16(xo, uint32_t(p >> 3) * K + uint32_t(p & 7) * 16, cs * kChunkK);
-    }
-#pragma unroll
-    for (int j = 0; j < kPi; ++j) {
-      const int p = tid + j * kDThreads;
-      if (BM * 4 % kDThreads == 0 || p < BM * 4)
-        x.i[j] = ld16(xi, uint32_t(p >> 2) * (K / 2) + uint32_t(p & 3) * 16, cs * (kChunkK / 2));
-    }
-    if (tid < BM) x.e = ld_ea4(ea, uint32_t(tid) * (K / 32), cs, K);
-  };
-  auto store_x = [&](int buf, const XRegs& x) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < kPo; ++j) {
-      const int p = tid + j * kDThreads;
-      *reinterpret_cast<v4i*>(&xo_s[buf][(p >> 3) * kRowO + (p & 7) * 16]) = x.o[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kPi; ++j) {
-      const int p = tid + j * kDThreads;
-      if (BM * 4 % kDThreads == 0 || p < BM * 4)
-        *reinterpret_cast<v4i*>(&xi_s[buf][(p >> 2) * kRowI + (p & 3) * 16]) = x.i[j];
-    }
-    if (tid < BM) ea_s[buf][tid] = x.e;
-  };
+  // One role's main loop (0: inliers, 1: outliers) and its part of the
+  // outputs, which end up in os (kOutRow floats per token) for the stores.
+  float* const os = reinterpret_cast<float*>(lds) + wave * (BM * kOutRow);
+  auto run = [&](auto role_tag) __attribute__((always_inline)) {
+    constexpr int ROLE = decltype(role_tag)::value;
+    typedef std::conditional_t<ROLE == 0, v16f, v16i> Acc;
 
-  // ---- the wave's weight stream, one chunk per stage
-  struct BRegs {
-    v4i bi[2];       // fp4 inlier fragments of the two 64-K steps
-    int sb[2];       // their e8m0 scales (block 2s + h of row col)
-    uint32_t hw[4][NP];  // outlier half-word pairs of the four 32-K steps, per plane
-  };
-  auto load_b = [&](int c, BRegs& st) __attribute__((always_inline)) {
-    const uint32_t cs = uint32_t(c);
+    // ---- the wave's tiles: dense inlier nibbles and their scales, or outlier half-words
+    __amdgpu_buffer_rsrc_t w0[TN], w1[TN];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      st.bi[s] = ld16(wn, uint32_t(s * 64 + lane) * 16u, cs * kDualNibBytesPerTC);
-      st.sb[s] = ld8(ws, uint32_t(s * 64 + lane), cs * kDualScaleBytesPerTC);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-        st.hw[u][p] = __builtin_amdgcn_raw_buffer_load_b32(
-            wo, uint32_t(p * kDualOutBytesPerTC) + uint32_t(u * 64 + lane) * 4u, cs * out_bytes_tc<NP>(), 0);
-  };
-
-  v16f acc[MS];
-  v16i acco[MS];
-#pragma unroll
-  for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) { acc[ms][e] = 0.f; acco[ms][e] = 0; }
-
-  auto compute = [&](int buf, const BRegs& st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const v8i b = {st.bi[s][0], st.bi[s][1], st.bi[s][2], st.bi[s][3], 0, 0, 0, 0};
-#pragma unroll
-      for (int ms = 0; ms < MS; ++ms) {
-        const int r = ms * 32 + col;
-        const v4i a4 = *reinterpret_cast<const v4i*>(&xi_s[buf][r * kRowI + s * 32 + h * 16]);
-        const int sa = int((ea_s[buf][r] >> (8 * (2 * s + h))) & 0xFFu);
-        const v8i av = {a4[0], a4[1], a4[2], a4[3], 0, 0, 0, 0};
-        // fp4 (format 4) on both sides, each lane half with its block's scale
-        acc[ms] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, b, acc[ms], 4, 4, 0, sa, 0, st.sb[s]);
+    for (int t = 0; t < TN; ++t) {
+      const bool ok = t0 + t < a.n_tiles;
+      const size_t tc = size_t(ok ? t0 + t : 0) * KC;
+      const uint32_t kc = ok ? uint32_t(KC) : 0u;
+      if constexpr (ROLE == 0) {
+        w0[t] = buffer_rsrc(a.blob + tc * kDualNibBytesPerTC, kc * kDualNibBytesPerTC);
+        w1[t] = buffer_rsrc(a.blob + a.scale_off + tc * kDualScaleBytesPerTC, kc * kDualScaleBytesPerTC);
+      } else {
+        w0[t] = buffer_rsrc(a.blob + a.out_off + tc * out_bytes_tc<NP>(), kc * out_bytes_tc<NP>());
       }
     }
+
+    // ---- activation staging of chunk c, in 16-byte pieces (8 per row of
+    //      A_o, 4 per row of A_i; LDS in order, the logical piece by the
+    //      row's swizzle).  From 64 tokens all threads move A_o's, with 32
+    //      the outlier waves; the inlier waves move A_i's and the scales.
+    //      The scales of a row are few bytes a chunk, and a request costs by
+    //      the lines it touches, so they come 16 bytes (four chunks) at a
+    //      time for a quarter of the rows: with chunk c the rows BM / 4 *
+    //      (c & 3) .. of the four chunks after chunk c's, eight lanes of each
+    //      wave on eight rows (fewer below 128 tokens, the rest repeat them).
+    constexpr bool kMoveO = MS >= 2 || ROLE == 1;
+    constexpr int kPo = !kMoveO ? 0 : MS >= 2 ? MS / 2 : 1;
+    constexpr int kPi = ROLE == 1 ? 0 : MS >= 2 ? MS / 2 : 1;
+    constexpr int kPieces = kPo + kPi + (ROLE == 0 ? 1 : 0);
+    struct XRegs { v4i o[kPo + 1]; v4i i[kPi + 1]; v4i e; };
+    constexpr int kOThreads = MS >= 2 ? 2 * kDThreads : kDThreads;
+    const int otid = tid % kOThreads, itid = tid % kDThreads;
+    const uint32_t ro = uint32_t(otid >> 3), ri = uint32_t(itid >> 2) % BM;
+    const uint32_t re = uint32_t(wave * 8 + (lane >> 3)) % (BM / 4);
+    const uint32_t vo = ro * K + uint32_t(((otid & 7) ^ swz_o(ro)) * 16);
+    const uint32_t vi = ri * (K / 2) + uint32_t(((itid & 3) ^ swz_i(ri)) * 16);
+    const uint32_t pi = (uint32_t(itid) % (BM * 4)) * 16;
+    auto load_e = [&](int c, v4i& e) __attribute__((always_inline)) {
+      const uint32_t row = re + uint32_t(c & 3) * (BM / 4) + eback;
+      e = ld16(ea, min(row * (K / 32) + uint32_t(cb + (c & ~3)) * 4, ebytes - 16), 0);
+    };
+    // A request that would reach past the end of the range was made early by
+    // d bytes; its bytes move down.  (Bytes past K are the next row's scales
+    // or unspecified: the weights there are zero codes.)
+    auto store_e = [&](int c, v4i e) __attribute__((always_inline)) {
+      const uint32_t r0 = re + uint32_t(c & 3) * (BM / 4);
+      const uint32_t off = (r0 + eback) * (K / 32) + uint32_t(cb + (c & ~3)) * 4;
+      const uint32_t d = off - min(off, ebytes - 16);
+      if (d & 8) { e[0] = e[2]; e[1] = e[3]; }
+      if (d & 4) { e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const v4i bo = outlier_bytes_np<NP>(st.hw[u]);
+      for (int j = 0; j < 4; ++j)
+        ea_s[(((c & ~3) + j) & 15) * BM + r0] = __builtin_amdgcn_alignbyte(e[j < 3 ? j + 1 : 3], e[j], d & 3);
+    };
+    auto load_x1 = [&](int c, XRegs& x, int j) __attribute__((always_inline)) {
+      const uint32_t cs = uint32_t(min(cb + c, last));
+      if (j < kPo) x.o[j] = ld16(xo, vo + uint32_t(j) * (kOThreads / 8) * K, cs * kChunkK);
+      else if (j < kPo + kPi) x.i[j - kPo] = ld16(xi, vi + uint32_t(j - kPo) * 32 * K, cs * (kChunkK / 2));
+      else load_e(c + 4, x.e);
+    };
+    auto store_x1 = [&](int buf, int c, const XRegs& x, int j) __attribute__((always_inline)) {
+      if (j < kPo) *reinterpret_cast<v4i*>(&xo_s[buf * kXo + (otid + j * kOThreads) * 16]) = x.o[j];
+      else if (j < kPo + kPi) *reinterpret_cast<v4i*>(&xi_s[buf * kXi + pi + (j - kPo) * kDThreads * 16]) = x.i[j - kPo];
+      else store_e(c + 4, x.e);
+    };
+    auto load_x = [&](int c, XRegs& x) __attribute__((always_inline)) {
 #pragma unroll
-      for (int ms = 0; ms < MS; ++ms) {
-        const v4i ao = *reinterpret_cast<const v4i*>(&xo_s[buf][(ms * 32 + col) * kRowO + u * 32 + h * 16]);
-        acco[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ao, bo, acco[ms], 0, 0, 0);
+      for (int j = 0; j < kPieces; ++j) load_x1(c, x, j);
+    };
+    auto store_x = [&](int buf, int c, const XRegs& x) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < kPieces; ++j) store_x1(buf, c, x, j);
+    };
+
+    // ---- the wave's weight stream, one 64-K step per stage
+    struct BIn {
+      v4i bi[TN];       // fp4 inlier fragments
+      uint32_t sb[TN];  // the dword that holds their e8m0 scale (block 2s + h of row col)
+    };
+    struct BOut {
+      uint32_t hw[TN][2][NP];  // outlier half-word pairs of the two 32-K steps, per plane
+    };
+    typedef std::conditional_t<ROLE == 0, BIn, BOut> BStep;
+    constexpr int kLoads = ROLE == 0 ? 2 * TN : 2 * TN * NP;  // requests per step
+    auto load_b1 = [&](int c, int s, BStep& st, int j) __attribute__((always_inline)) {
+      const uint32_t cs = uint32_t(cb + c);  // past the last chunk: reads 0
+      if constexpr (ROLE == 0) {
+        const int t = j >> 1;
+        if ((j & 1) == 0)
+          st.bi[t] = ld16(w0[t], uint32_t(s * 64 + lane) * 16u, cs * kDualNibBytesPerTC);
+        else
+          // (a byte load would be narrowed to 8 bits across the loop, and its
+          // widening waits for the load at the top of the chunk; shifted at use)
+          st.sb[t] = __builtin_amdgcn_raw_buffer_load_b32(w1[t], uint32_t(s * 64 + (lane & ~3)),
+                                                          cs * kDualScaleBytesPerTC, 0);
+      } else {
+        const int t = j / (2 * NP), u = (j / NP) & 1, p = j % NP;
+        st.hw[t][u][p] = __builtin_amdgcn_raw_buffer_load_b32(
+            w0[t], uint32_t(p * kDualOutBytesPerTC) + uint32_t((2 * s + u) * 64 + lane) * 4u, cs * out_bytes_tc<NP>(), 0);
+      }
+    };
+    auto load_b = [&](int c, int s, BStep& st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) load_b1(c, s, st, j);
+    };
+
+    // ---- activation fragments of one (64-K step, 32-token sub-tile)
+    struct FIn { v4i i; uint32_t e; };
+    struct FOut { v4i o0, o1; };
+    typedef std::conditional_t<ROLE == 0, FIn, FOut> Frag;
+    uint32_t ai[2], ao[2][2];  // LDS byte offsets of row col
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      ai[s] = uint32_t(col * (kChunkK / 2) + (((2 * s + h) ^ swz_i(col)) << 4));
+#pragma unroll
+      for (int u = 0; u < 2; ++u) ao[s][u] = uint32_t(col * kChunkK + (((4 * s + 2 * h + u) ^ swz_o(col)) << 4));
+    }
+    auto read_frag = [&](int buf, int c, int s, int ms, Frag& f) __attribute__((always_inline)) {
+      if constexpr (ROLE == 0) {
+        f.i = *reinterpret_cast<const v4i*>(&xi_s[buf * kXi + ai[s] + ms * 32 * (kChunkK / 2)]);
+        f.e = ea_s[(c & 15) * BM + ms * 32 + col];  // (shifted where it is used, after the wait for the slot's reads)
+      } else {
+        f.o0 = *reinterpret_cast<const v4i*>(&xo_s[buf * kXo + ao[s][0] + ms * 32 * kChunkK]);
+        f.o1 = *reinterpret_cast<const v4i*>(&xo_s[buf * kXo + ao[s][1] + ms * 32 * kChunkK]);
+      }
+    };
+
+    Acc acc[TN][MS];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][ms][e] = 0;
+
+    XRegs X[2];           // [chunk parity]
+    BStep B[2][2];        // [chunk parity][step]
+    SparseOut so[2][TN];  // [step]; outliers
+    Frag F[2];
+    auto expand = [&](const BStep& w, int t, SparseOut& d) __attribute__((always_inline)) {
+      if constexpr (ROLE == 1) d = sparse_outliers<NP>(w.hw[t][0], w.hw[t][1]);
+    };
+    // the prologue's requests in the loop's own order, which the compiler's
+    // wait counts at the loop head would otherwise be tightened to
+    {
+      XRegs P0, P1;
+      v4i e0[4];  // the scales of chunks 0..3, every quarter of the rows
+      load_x(0, P0);
+      load_x(1, P1);
+      if constexpr (ROLE == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_e(q, e0[q]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        load_x(2 + p, X[p]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 2 - p; ++s) load_b(p, s, B[p][s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      store_x(0, 0, P0);
+      store_x(1, 1, P1);
+      if constexpr (ROLE == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) store_e(q, e0[q]);
       }
     }
+    __syncthreads();
+    read_frag(0, 0, 0, 0, F[0]);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) expand(B[0][0], t, so[0][t]);
+
+    // One chunk is 2 MS slots, one per (step, sub-tile).  A slot reads the
+    // next slot's activation fragment, multiplies its own by the TN tiles,
+    // and carries a share of the other work: the next step's sparse operands,
+    // the weights of chunk c + 2 into the registers the previous step freed,
+    // and chunk c + 2's activations from registers to LDS and c + 4's into
+    // them.  Slots are kept apart for the scheduler, which would otherwise
+    // sink products past the barrier.
+    int b0 = 0, b1 = 1, b2 = 2;  // LDS buffers of chunks c, c + 1, c + 2
+    auto chunk = [&](int c, BStep (&W)[2], BStep (&V)[2], XRegs& x) __attribute__((always_inline)) {
+      constexpr int kSlots = 2 * MS;
+#pragma unroll
+      for (int k = 0; k < kSlots; ++k) {
+        const int s = k / MS, ms = k % MS;
+        const Frag& f = F[k & 1];
+        Frag& nx = F[(k + 1) & 1];
+        if (k + 1 < kSlots) read_frag(b0, c, (k + 1) / MS, (k + 1) % MS, nx);
+        else read_frag(b1, c + 1, 0, 0, nx);
+        // the other step's operands: step 1 of this chunk, or step 0 of the next
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+          if (ms == (MS >= 4 ? 1 + t : MS - 1)) expand(s == 0 ? W[1] : V[0], t, so[1 - s][t]);
+#pragma unroll
+        for (int j = k * kPieces / kSlots; j < (k + 1) * kPieces / kSlots; ++j) {
+          store_x1(b2, c + 2, x, j);
+          load_x1(c + 4, x, j);
+        }
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+          if constexpr (ROLE == 0) {
+            const v8i xa = {f.i[0], f.i[1], f.i[2], f.i[3], 0, 0, 0, 0};
+            const v8i wa = {W[s].bi[t][0], W[s].bi[t][1], W[s].bi[t][2], W[s].bi[t][3], 0, 0, 0, 0};
+            // fp4 (format 4) on both sides, each lane half with its block's scale
+            acc[t][ms] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                wa, xa, acc[t][ms], 4, 4, 0, int(W[s].sb[t] >> (8 * (lane & 3))), 0, int(f.e >> (16 * s + 8 * h)));
+          } else {
+            const v8i xb = __builtin_shufflevector(f.o0, f.o1, 0, 1, 2, 3, 4, 5, 6, 7);
+            const v4i wv = {int(so[s][t].v[0]), int(so[s][t].v[1]), int(so[s][t].v[2]), int(so[s][t].v[3])};
+            acc[t][ms] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(wv, xb, acc[t][ms], int(so[s][t].idx), 0, 0);
+          }
+        }
+        // the step that just ended leaves its registers to a later chunk's
+#pragma unroll
+        for (int j = ms * kLoads / MS; j < (ms + 1) * kLoads / MS; ++j) {
+          if (s == 0) load_b1(c + 1, 1, V[1], j);
+          else load_b1(c + 2, 0, W[0], j);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+      const int t = b0;
+      b0 = b1;
+      b1 = b2;
+      b2 = t;
+    };
+    int c = 0;
+    for (; c + 1 < cn; c += 2) {  // one exit, so the accumulators stay in place
+      chunk(c, B[0], B[1], X[0]);
+      chunk(c + 1, B[1], B[0], X[1]);
+    }
+    if (c < cn) chunk(c, B[0], B[1], X[0]);  // a last chunk of even rank
+
+    // ---- the second K group's accumulators join the first's
+    if constexpr (KG == 2) {
+      typedef std::conditional_t<ROLE == 0, float, int> Elem;
+      Elem* const red = reinterpret_cast<Elem*>(lds + kOutBytes) + (ROLE * kDWaves + wave) * (TN * MS * 16 * 64) + lane;
+      if (kg == 1) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+          for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) red[((t * MS + ms) * 16 + e) * 64] = acc[t][ms][e];
+      }
+      __syncthreads();
+      if (kg == 0) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+          for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][ms][e] += red[((t * MS + ms) * 16 + e) * 64];
+      }
+    }
+    // ---- lane (col, h) holds token 32 ms + col, outputs 8 j + 4 h .. + 3 of
+    //      each tile: the outlier waves leave s_o * P in LDS, the inlier
+    //      waves turn that into the output in place
+    if constexpr (ROLE == 1) {
+      if (kg == 0) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+          const float* sop = reinterpret_cast<const float*>(a.blob + a.rows_off) + min(t0 + t, a.n_tiles - 1) * kTileN + 4 * h;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float4 q = *reinterpret_cast<const float4*>(sop + 8 * j);
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms)
+              *reinterpret_cast<float4*>(&os[(ms * 32 + col) * kOutRow + t * kTileN + 8 * j + 4 * h]) =
+                  make_float4(q.x * float(acc[t][ms][4 * j]), q.y * float(acc[t][ms][4 * j + 1]),
+                              q.z * float(acc[t][ms][4 * j + 2]), q.w * float(acc[t][ms][4 * j + 3]));
+          }
+        }
+      }
+      __syncthreads();
+    } else {
+      const __amdgpu_buffer_rsrc_t sr = buffer_rsrc(a.s_a + m0, rows * 4u);
+      float sa[MS];
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms)
+        sa[ms] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sr, uint32_t(ms * 32 + col) * 4u, 0, 0));
+      __syncthreads();
+      if (kg == 0) {
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+          for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              float4* p = reinterpret_cast<float4*>(&os[(ms * 32 + col) * kOutRow + t * kTileN + 8 * j + 4 * h]);
+              const float4 q = *p;
+              *p = make_float4(fmaf(sa[ms], q.x, acc[t][ms][4 * j]), fmaf(sa[ms], q.y, acc[t][ms][4 * j + 1]),
+                               fmaf(sa[ms], q.z, acc[t][ms][4 * j + 2]), fmaf(sa[ms], q.w, acc[t][ms][4 * j + 3]));
+            }
+      }
+    }
+    __syncthreads();
   };
+  if (wave8 < kDWaves) run(std::integral_constant<int, 0>{});
+  else run(std::integral_constant<int, 1>{});
 
-  // ---- pipeline: chunk c in LDS buffer c & 1 and weight stage c & 1; the
-  //      activations of chunk c + 1 wait in registers and are stored after
-  //      the products of chunk c.  Loads past the last chunk re-read it.
-  XRegs X;
-  BRegs B0, B1;
-  load_x(0, X);
-  load_b(0, B0);
-  store_x(0, X);
-  load_x(min(1, last), X);
-  load_b(min(1, last), B1);
-  __syncthreads();
-  int c = 0;
-  for (; c + 1 < KC; c += 2) {  // one exit, so the accumulators stay in place
-    compute(0, B0);
-    load_b(min(c + 2, last), B0);
-    store_x(1, X);  // chunk c + 1 (buffer 1 was last read before the previous barrier)
-    load_x(min(c + 2, last), X);
-    __syncthreads();
-    compute(1, B1);
-    load_b(min(c + 3, last), B1);
-    store_x(0, X);  // chunk c + 2
-    load_x(min(c + 3, last), X);
-    __syncthreads();
-  }
-  if (c < KC) compute(0, B0);  // a last chunk of even rank
-
-  if (!tile_ok) return;
-  const int n = tile * kTileN + col;
-  if (n >= a.N) return;
-  const float so = reinterpret_cast<const float*>(a.blob + a.rows_off)[n];
-  const RowScales<MS> rs = load_row_scales<MS>(a.s_a, a.M, m0, h);
+  // ---- the waves that share an output group store an equal part of its tokens.  A request that
+  //      touches many rows of Y costs by the row (four cycles each), so a
+  //      wave stores whole lines of a few rows.
+  const int nw = t0 * kTileN, n_left = a.N - nw;  // the group's outputs
   const OutRows yr = out_rows(a.Y, a.y_bf16, a.M, a.N, m0, BM);
-#pragma unroll
-  for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      store_out(yr, a.N, n, ms, e, h, fmaf(rs.v[ms][e], so * float(acco[ms][e]), acc[ms][e]));
+  constexpr int kRows = BM / (2 * KG);
+  const int r_lo = (2 * kg + (wave8 >> 2)) * kRows;
+  if (a.y_vec) {  // four outputs a lane, 256 / kOutW tokens a request
+    constexpr int kL = kOutW / 4;  // lanes per token
+    const int n = 4 * (lane % kL);
+#pragma unroll 8
+    for (int r = r_lo; r < r_lo + kRows; r += 64 / kL) {
+      const float4 v = *reinterpret_cast<const float4*>(&os[(r + lane / kL) * kOutRow + n]);
+      if (n < n_left) store_out4(yr, uint32_t(r + lane / kL) * uint32_t(a.N) + uint32_t(nw + n), v);
+    }
+  } else {
+    const int n = lane % kOutW;
+#pragma unroll 4
+    for (int r = r_lo; r < r_lo + kRows; r += 64 / kOutW) {
+      const int row = r + lane / kOutW;
+      const float v = os[row * kOutRow + n];
+      if (n < n_left) {
+        const uint32_t idx = uint32_t(row) * uint32_t(a.N) + uint32_t(nw + n);
+        if (yr.bf16) __builtin_amdgcn_raw_buffer_store_b16(bf16_bits(v), yr.r, idx * 2u, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), yr.r, idx * 4u, 0, 0);
+      }
+    }
+  }
 }
 
 // Split-K form for few tokens (up to 32, more on narrow layers): one 32-row tile per workgroup, its
@@ -382,38 +643,45 @@ __global__ __launch_bounds__(NW * 64, 2) void dual_splitk_kernel(DualArgs a) {
   for (int e = 0; e < 16; ++e) store_out(yr, a.N, n, 0, e, h, fmaf(rs.v[0][e], so * float(acco[e]), acc[e]));
 }
 
-template <int MS, int NP>
-hipError_t launch_ms(const DualArgs& a, hipStream_t st) {
-  const dim3 grid(unsigned((a.n_tiles + kDWaves - 1) / kDWaves), unsigned((a.M + 32 * MS - 1) / (32 * MS)));
-  hipLaunchKernelGGL((dual_mfma_kernel<MS, NP>), grid, dim3(kDThreads), 0, st, a);
+template <int MS, int TN, int NP, int KG>
+hipError_t launch_tiled(DualArgs a, hipStream_t st) {
+  a.groups = (a.n_tiles + kDWaves * TN - 1) / (kDWaves * TN);
+  a.m_blocks = (a.M + 32 * MS - 1) / (32 * MS);
+  const dim3 grid(unsigned(a.groups) * unsigned(a.m_blocks));
+  hipLaunchKernelGGL((dual_tiled_kernel<MS, TN, NP, KG>), grid, dim3(KG * 2 * kDThreads), 0, st, a);
   return hipGetLastError();
 }
 
-// The split-K form up to 32 tokens, and beyond while its grid (one tile x 32
-// tokens per workgroup) stays within one round, or two on long rows
-// (measured: 4096x4096 at M = 48 / 64 takes 11.9 / 12.0 us against 18.8 in
-// tiles, at 96 21.1 against 19.0; 4096x11008 at M = 64 / 96 / 128 takes 23.1
-// / 41.7 / 42.6 against 48.6 / 48.5 / 48.7; 11008x4096 at M = 48 27.4
-// against 22.6); else the tiled form (NP outlier planes).
+// The split-K form while its grid (one tile x 32 tokens per workgroup) stays
+// within one round, and up to 8 tokens: its waves gather activation rows
+// themselves, which costs by the row (4096x4096 at M = 16 / 64: 9.4 / 12.7 us
+// against 12.2 / 12.6 in tiles; 11008x4096, 344 workgroups, at M = 4 / 16 /
+// 32: 11.7 / 15.9 / 21.7 against 12.4 / 12.5 / 13.2).  Else the tiled form
+// of least cost, with these costs of a round of 256 workgroups in half
+// microseconds at K = 4096 (other K scale alike): 32 tokens x 128 outputs 27;
+// 64 x 128 33, and 24 for each further round (two run per CU); 64 x 256 46;
+// 128 x 256 66.  Measured (the four in this order): 4096x4096 at M = 256 / 512
+// / 1024 / 2048: 14.2, 16.6, 21.2, 29.2 / 26.1, 19.6, 23.8, 30.8 / 53.7, 32.3,
+// 28.2, 35.6 / -, 60.7, 55.6, 46.0; 11008x4096 at M = 128 / 256 / 512: 24.9,
+// 17.7, 21.9, 29.6 / 37.2, 27.7, 24.4, 31.5 / 71.0, 42.5, 46.3, 36.7;
+// 4096x11008 at M = 256 / 768: 28.8, 35.8, 45.9, 63.6 / 81.2, 66.1, 52.8, 68.7.
 template <int NP>
 hipError_t launch_np(const DualArgs& a, hipStream_t st) {
-  const int64_t split_grid = int64_t(a.n_tiles) * ((a.M + 31) / 32);
-  if (a.M <= 32 || split_grid <= 256 || (a.K >= 8192 && split_grid <= 512)) {
-    const dim3 grid(unsigned(a.n_tiles), unsigned((a.M + 31) / 32));
+  const int64_t M = a.M;
+  // (the tiled form reads the activation scales 16 bytes at a time)
+  if (M <= 8 || int64_t(a.n_tiles) * ((M + 31) / 32) <= 256 || M * (a.K / 32) < 16) {
+    const dim3 grid(unsigned(a.n_tiles), unsigned((M + 31) / 32));
     hipLaunchKernelGGL((dual_splitk_kernel<4, NP>), grid, dim3(4 * 64), 0, st, a);
     return hipGetLastError();
   }
-  // Tokens per workgroup: 32, 64 or 128 (one, two or four sub-tiles per
-  // wave).  Larger blocks reuse every weight fragment for more tokens but
-  // give fewer workgroups; the smallest block that leaves the GPU full wins.
-  // Measured on the LLaMA-7B shapes: 4096x4096 at M = 128/256 takes 19/21 us
-  // with 32-token blocks against 31/32 us with 128; 11008x4096 at M = 512
-  // takes 60 us with 64-token blocks against 73 us with 128.
-  const int64_t groups = (a.n_tiles + kDWaves - 1) / kDWaves;
-  const int64_t M = a.M;
-  if (groups * ((M + 31) / 32) <= 256) return launch_ms<1, NP>(a, st);
-  if (groups * ((M + 63) / 64) <= 1024 && groups * ((M + 127) / 128) < 512) return launch_ms<2, NP>(a, st);
-  return launch_ms<4, NP>(a, st);
+  const int64_t g4 = (a.n_tiles + 3) / 4, g8 = (a.n_tiles + 7) / 8;
+  const auto rounds = [](int64_t wgs) { return (wgs + 255) / 256; };
+  const int64_t c11 = 27 * rounds(g4 * ((M + 31) / 32)), c21 = 9 + 24 * rounds(g4 * ((M + 63) / 64));
+  const int64_t c22 = 46 * rounds(g8 * ((M + 63) / 64)), c42 = 66 * rounds(g8 * ((M + 127) / 128));
+  if (c11 <= c21 && c11 <= c22 && c11 <= c42) return launch_tiled<1, 1, NP, 2>(a, st);
+  if (c21 <= c22 && c21 <= c42) return launch_tiled<2, 1, NP, 1>(a, st);
+  if (c22 <= c42) return launch_tiled<2, 2, NP, 1>(a, st);
+  return launch_tiled<4, 2, NP, 1>(a, st);
 }
 
 }  // namespace
@@ -425,6 +693,7 @@ hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, c
   DualArgs a{Xo, s_a, Xi, Ea, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles),
              L.out_off, L.scale_off, L.rows_off};
   a.y_bf16 = c.y_bf16;
+  a.y_vec = N % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
   if (dual_decode_fits(M, N, K)) return launch_dual_decode(c, Xo, s_a, Xi, Ea, M, blob, N, K, Y, st);
   return L.out_planes == 2 ? launch_np<2>(a, st) : launch_np<1>(a, st);
 }

@@ -39,6 +39,18 @@ __host__ __device__ __forceinline__ void tile_work(int b, int G, int MB, int& gr
   }
 }
 
+// (tile group, token block) of workgroup b in a grid of G x MB, in blocks of
+// up to 8 token blocks by all groups: the 32 compute units of an XCD work on
+// about 4 groups x 8 token blocks at a time, so that what its L2 fetches is
+// near the least for that many tiles.  A bijection on [0, G * MB).
+__host__ __device__ __forceinline__ void square_work(int b, int G, int MB, int& group, int& mblock) {
+  const int L = xcd_contiguous(b, G * MB);
+  const int sup = L / (G * 8), rest = L - sup * G * 8;
+  const int w = min(8, MB - sup * 8);  // token blocks of this super-block
+  group = rest / w;
+  mblock = sup * 8 + (rest - group * w);
+}
+
 hipError_t launch_act_quant(const Cfg& c, const void* X, int x_dtype, int64_t M, int64_t K,
                             uint8_t* Xq, float* s_a, hipStream_t st);
 // Dual family: int8 A_o (Xo, s_a) and MXFP4 A_i (Xi: [M][K/2] nibbles, Ea: [M][K/32] e8m0).

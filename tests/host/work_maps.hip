@@ -43,6 +43,21 @@ int main() {
       }
     }
   }
+  // square_work: likewise, in super-blocks of up to 8 token blocks.
+  for (int G = 1; G <= 180; ++G) {
+    for (int MB = 1; MB <= 40; ++MB) {
+      std::vector<int> seen(G * MB, 0);
+      for (int b = 0; b < G * MB; ++b) {
+        int g = -1, mb = -1;
+        sdq::square_work(b, G, MB, g, mb);
+        if (g < 0 || g >= G || mb < 0 || mb >= MB || seen[g * MB + mb]++) {
+          std::printf("square_work(%d, G=%d, MB=%d) = (%d, %d): out of range or repeated\n", b, G, MB, g, mb);
+          return 1;
+        }
+        ++checked;
+      }
+    }
+  }
   std::printf("work maps ok: %ld workgroups checked\n", checked);
   return 0;
 }

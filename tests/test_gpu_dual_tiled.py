@@ -1,0 +1,59 @@
+"""GPU: the dual family's tiled kernel at the sizes where it can go wrong, for
+each of its workgroup shapes, against the fp64 oracle.
+
+The launcher picks the shape by grid: 32 tokens x 128 outputs (two K groups
+per workgroup), 64 x 128, 64 x 256 and 128 x 256.  For each: ragged tokens
+and outputs, one chunk of K, an odd number of chunks, K that is not a whole
+chunk (with rows of scales that are not whole dwords), one and two outlier
+planes, fp32 and bf16 outputs, an output that is not 16-byte aligned.  The
+tolerance is that of test_gpu_dual (fp32 sums of exact products; a bf16
+output adds its half ulp).
+"""
+import numpy as np
+import pytest
+
+import synth
+from oracle import sdq as S
+from tests.gpu_util import dual_term_tol, rel_errors, say, torch_cuda
+
+import paper_2406_13868_amd as sdq
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # M, N, K
+    (9, 8225, 160), (16, 8224, 32), (32, 8200, 416), (33, 8193, 128),     # 32 x 128
+    (130, 8196, 96), (321, 4129, 288), (384, 4096, 640),                  # 64 x 128
+    (513, 8225, 160), (700, 4100, 256),                                   # 64 x 256
+    (1100, 8193, 96), (2049, 4100, 416),                                  # 128 x 256
+]
+
+
+@pytest.mark.parametrize("n_o,n_i", [(1, 6), (2, 4)])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_tiled_shapes_match_oracle(M, N, K, n_o, n_i, y_dtype):
+    torch = torch_cuda()
+    cfg = sdq.Config("dual", n_o, 8, "int8", n_i, 8, "e2m1", "int8", y_dtype=y_dtype)
+    cfg_o = S.Config("dual", n_o, 8, "int8", n_i, 8, "e2m1", "int8+e2m1")
+    X, W = synth.make_x(2, M, K), synth.make_w(2, 0, N, K)
+    X[M // 2] = 0.0  # an all-zero token
+    say("dual tiled", M, N, K, n_o, y_dtype)
+    blob = torch.from_numpy(sdq.pack(W, cfg)).cuda()
+    q = sdq.quantize_act_dual(torch.from_numpy(X).cuda(), cfg)
+    # an output one element into its allocation: 4-byte (bf16: 4 of 8) aligned only
+    buf = torch.full((M * N + 4,), 7.0, dtype=cfg.y_torch_dtype(), device="cuda")
+    skip = 1 if y_dtype == "f32" else 2
+    outs = [sdq.gemm_dual(*q, blob, N, K, cfg),
+            sdq.gemm_dual(*q, blob, N, K, cfg, out=buf[skip:skip + M * N].view(M, N))]
+    torch.cuda.synchronize()
+    Yref, (Ao, Ai), (s_ao, Ea), L = S.reference(X, W, cfg_o)
+    A_o, A_i = S.dequant_act_dual(Ao, s_ao, Ai, Ea)
+    T = np.abs(A_o) @ np.abs(S.dequant_outliers(L)).T + np.abs(A_i) @ np.abs(S.dequant_inliers(L)).T
+    for Y in outs:
+        Yn = Y.float().cpu().numpy().astype(np.float64)
+        tol = dual_term_tol(K) * T + (np.abs(Yref) * 2.0 ** -8 if y_dtype == "bf16" else 0.0)
+        bad = np.abs(Yn - Yref) > tol + 1e-30
+        assert not bad.any(), f"{bad.sum()} outputs off, first at {np.argwhere(bad)[0]}, {rel_errors(Yn, Yref)}"
+    assert torch.equal(outs[0], outs[1])
+    # nothing is written outside the output
+    assert (buf[:skip] == 7.0).all() and (buf[skip + M * N:] == 7.0).all()

@@ -291,6 +291,16 @@ sdq_status sdq_linear(const sdq_config* cfg, const void* X, int32_t x_dtype, int
                       void* Xq, float* s_a, const void* packed, int64_t N, int64_t K, void* Y,
                       void* stream);
 
+/* sdq_linear with a device workspace, as sdq_gemm_ws is sdq_gemm with one: the
+ * results of sdq_quantize_act followed by sdq_gemm_ws with SDQ_PATH_AUTO where
+ * that path takes a workspace, and sdq_linear's otherwise.  workspace and
+ * ws_bytes as in sdq_gemm_ws (NULL and 0 where sdq_gemm_workspace_size with
+ * SDQ_PATH_AUTO says 0; SDQ_ERR_BUFFER_TOO_SMALL, before any GPU work, where it
+ * needs more). */
+sdq_status sdq_linear_ws(const sdq_config* cfg, const void* X, int32_t x_dtype, int64_t M,
+                         void* Xq, float* s_a, const void* packed, int64_t N, int64_t K, void* Y,
+                         void* workspace, size_t ws_bytes, void* stream);
+
 /* The path sdq_gemm takes for this configuration and M (SDQ_PATH_DECODE or
  * SDQ_PATH_MFMA). */
 sdq_status sdq_gemm_path(const sdq_config* cfg, int64_t M, int64_t N, int64_t K, int32_t* path);

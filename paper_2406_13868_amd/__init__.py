@@ -16,6 +16,7 @@ from __future__ import annotations
 
 import ctypes as C
 import dataclasses
+import functools
 from typing import Dict, Optional
 
 import numpy as np
@@ -137,8 +138,22 @@ class Config:
                                _lib.SCALE[self.sfmt_i],
                                {"f32": DTYPE_F32, "bf16": DTYPE_BF16}[self.y_dtype], self.qv_i)
 
+    # What a call hands to the library, made once per Config object (its fields
+    # never change): the C structure by reference, and the pack sizes of the
+    # shapes it was used with.
+    @functools.cached_property
+    def _ref(self):
+        return C.byref(self.c())
+
+    @functools.cached_property
+    def _sizes(self) -> dict:
+        return {}
+
+    def __getstate__(self):  # the fields alone: a reference cannot be copied or pickled
+        return {f.name: getattr(self, f.name) for f in dataclasses.fields(self)}
+
     def y_torch_dtype(self):
-        import torch
+        torch = _torch()
         return torch.bfloat16 if self.y_dtype == "bf16" else torch.float32
 
 
@@ -150,9 +165,19 @@ def check(cfg: Config, N: int, K: int) -> None:
     _lib.check(_lib.lib().sdq_check(C.byref(cfg.c()), N, K), "sdq_check")
 
 
+_MAX_SIZES = 256  # shapes a Config remembers the pack size of
+
+
 def pack_size(cfg: Config, N: int, K: int) -> int:
+    sizes = cfg._sizes
+    have = sizes.get((N, K))
+    if have is not None:
+        return have
     n = C.c_size_t()
-    _lib.check(_lib.lib().sdq_pack_size(C.byref(cfg.c()), N, K, C.byref(n)), "sdq_pack_size")
+    _lib.check(_lib.lib().sdq_pack_size(cfg._ref, N, K, C.byref(n)), "sdq_pack_size")
+    if len(sizes) >= _MAX_SIZES:
+        sizes.clear()
+    sizes[(N, K)] = n.value
     return n.value
 
 
@@ -220,45 +245,61 @@ def unpack_dense(blob: np.ndarray, cfg: Config, N: int, K: int) -> Dict[str, np.
 
 
 # ----------------------------------------------------------------- device side
-def _stream(stream) -> C.c_void_p:
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+# A call's host time is its floor at decode sizes (one token through a 4096 x
+# 4096 layer: 5 us on the GPU), so the checks below compare without building
+# tuples or sets, and torch is looked up once.
+_torch_mod = None
 
 
-def _dev(t, what: str):
+def _torch():
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch()
+    try:  # the current device's current stream without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
+
+
+def _dev(t, what: str) -> int:
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{what} must be a contiguous CUDA (HIP) tensor")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _need(t, shape, dtype, what: str):
     """Check a caller-supplied tensor before its pointer reaches the library,
     which cannot see sizes: exact shape and dtype (placement and contiguity are
     checked where the pointer is taken)."""
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise ValueError(f"{what} must be a torch tensor")
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
+    if t.shape != shape or t.dtype != dtype:
         raise ValueError(f"{what} must be {list(shape)} {dtype}, got {list(t.shape)} {t.dtype}")
     return t
 
 
 def _need_bytes(t, nbytes: int, what: str):
     """A raw byte buffer (packed weights, workspace): at least nbytes."""
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise ValueError(f"{what} must be a torch tensor")
     if not t.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
-    have = t.numel() * t.element_size()
+    have = t.nbytes
     if have < nbytes:
         raise ValueError(f"{what} holds {have} bytes, needs {nbytes}")
     return t
 
 
 def _x_dtype(X):
-    import torch
+    torch = _torch()
     if X.dtype == torch.float32:
         return DTYPE_F32
     if X.dtype == torch.bfloat16:
@@ -266,26 +307,27 @@ def _x_dtype(X):
     raise ValueError("X must be float32 or bfloat16")
 
 
-def _same_device(*ts):
-    devs = {t.device for t in ts if t is not None}
-    if len(devs) > 1:
-        raise ValueError(f"tensors are on different devices: {sorted(map(str, devs))}")
+def _same_device(first, *ts):
+    dev = first.device
+    for t in ts:
+        if t is not None and t.device != dev:
+            devs = {t.device for t in (first, *ts) if t is not None}
+            raise ValueError(f"tensors are on different devices: {sorted(map(str, devs))}")
 
 
 def _out(out, M: int, N: int, cfg: Config, device):
     """The GEMM output: `out` checked against [M, N] of cfg's output dtype, or a new tensor."""
-    import torch
     dt = cfg.y_torch_dtype()
     if out is None:
-        return torch.empty((M, N), dtype=dt, device=device)
-    if tuple(out.shape) != (M, N) or out.dtype != dt:
+        return _torch().empty((M, N), dtype=dt, device=device)
+    if out.shape != (M, N) or out.dtype != dt:
         raise ValueError(f"out must be [{M}, {N}] {dt}, got {list(out.shape)} {out.dtype}")
     return out
 
 
 def quantize_act(X, cfg: Config, out=None, scales=None, stream=None):
     """Per-token activation quantization on the GPU: returns (Xq uint8, s_a f32)."""
-    import torch
+    torch = _torch()
     if X.dim() != 2:
         raise ValueError("X must be [M, K]")
     M, K = X.shape
@@ -295,7 +337,7 @@ def quantize_act(X, cfg: Config, out=None, scales=None, stream=None):
     _need(Xq, (M, K), torch.uint8, "Xq")
     _need(s_a, (M,), torch.float32, "s_a")
     _same_device(X, Xq, s_a)
-    _lib.check(_lib.lib().sdq_quantize_act(C.byref(cfg.c()), _dev(X, "X"), dt, M, K,
+    _lib.check(_lib.lib().sdq_quantize_act(cfg._ref, _dev(X, "X"), dt, M, K,
                                            _dev(Xq, "Xq"), _dev(s_a, "s_a"), _stream(stream)),
                "sdq_quantize_act")
     return Xq, s_a
@@ -305,7 +347,7 @@ def quantize_act_dual(X, cfg: Config, out=None, stream=None):
     """The dual family's activations on the GPU: returns (Xq_o uint8 [M, K],
     s_a_o f32 [M], Xq_i uint8 [M, K/2] fp4 nibbles, e_a_i uint8 [M, K/32] e8m0),
     written into `out` (a tuple of those four tensors) when given."""
-    import torch
+    torch = _torch()
     if X.dim() != 2:
         raise ValueError("X must be [M, K]")
     M, K = X.shape
@@ -323,7 +365,7 @@ def quantize_act_dual(X, cfg: Config, out=None, stream=None):
     _need(Xi, (M, K // 2), torch.uint8, "Xq_i")
     _need(Ea, (M, K // 32), torch.uint8, "e_a_i")
     _same_device(X, Xo, s_a, Xi, Ea)
-    _lib.check(_lib.lib().sdq_quantize_act_dual(C.byref(cfg.c()), _dev(X, "X"), dt, M, K, _dev(Xo, "Xq_o"),
+    _lib.check(_lib.lib().sdq_quantize_act_dual(cfg._ref, _dev(X, "X"), dt, M, K, _dev(Xo, "Xq_o"),
                                                 _dev(s_a, "s_a_o"), _dev(Xi, "Xq_i"), _dev(Ea, "e_a_i"),
                                                 _stream(stream)), "sdq_quantize_act_dual")
     return Xo, s_a, Xi, Ea
@@ -331,7 +373,7 @@ def quantize_act_dual(X, cfg: Config, out=None, stream=None):
 
 def gemm_dual(Xo, s_a, Xi, Ea, packed, N: int, K: int, cfg: Config, out=None, stream=None):
     """The dual family's GEMM on the GPU (output [M, N], fp32 or bf16 by cfg.y_dtype)."""
-    import torch
+    torch = _torch()
     if Xo.dim() != 2:
         raise ValueError("Xq_o must be [M, K]")
     M = Xo.shape[0]
@@ -342,7 +384,7 @@ def gemm_dual(Xo, s_a, Xi, Ea, packed, N: int, K: int, cfg: Config, out=None, st
     _need_bytes(packed, pack_size(cfg, N, K), "packed")
     Y = _out(out, M, N, cfg, Xo.device)
     _same_device(Xo, s_a, Xi, Ea, packed, Y)
-    _lib.check(_lib.lib().sdq_gemm_dual(C.byref(cfg.c()), _dev(Xo, "Xq_o"), _dev(s_a, "s_a_o"),
+    _lib.check(_lib.lib().sdq_gemm_dual(cfg._ref, _dev(Xo, "Xq_o"), _dev(s_a, "s_a_o"),
                                         _dev(Xi, "Xq_i"), _dev(Ea, "e_a_i"), M, _dev(packed, "packed"),
                                         N, K, _dev(Y, "Y"), _stream(stream)), "sdq_gemm_dual")
     return Y
@@ -351,7 +393,7 @@ def gemm_dual(Xo, s_a, Xi, Ea, packed, N: int, K: int, cfg: Config, out=None, st
 def gemm_workspace_size(cfg: Config, M: int, N: int, K: int, path: int = PATH_AUTO) -> int:
     """Device workspace bytes the GEMM takes for this shape and path (0: none)."""
     b = C.c_size_t()
-    _lib.check(_lib.lib().sdq_gemm_workspace_size(C.byref(cfg.c()), M, N, K, path, C.byref(b)),
+    _lib.check(_lib.lib().sdq_gemm_workspace_size(cfg._ref, M, N, K, path, C.byref(b)),
                "sdq_gemm_workspace_size")
     return b.value
 
@@ -364,7 +406,7 @@ def gemm(Xq, s_a, packed, N: int, K: int, cfg: Config, out=None, path: int = PAT
     INT family's split-K path for tens to hundreds of tokens) use
     `workspace` (a uint8 CUDA tensor of at least gemm_workspace_size bytes)
     or a fresh one."""
-    import torch
+    torch = _torch()
     if Xq.dim() != 2:
         raise ValueError("Xq must be [M, K]")
     M = Xq.shape[0]
@@ -375,14 +417,14 @@ def gemm(Xq, s_a, packed, N: int, K: int, cfg: Config, out=None, path: int = PAT
     _same_device(Xq, s_a, packed, Y, workspace)
     ws_bytes = gemm_workspace_size(cfg, M, N, K, path)
     if ws_bytes == 0 and path not in (PATH_DENSE, PATH_SPLITK):
-        _lib.check(_lib.lib().sdq_gemm_ex(C.byref(cfg.c()), _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
+        _lib.check(_lib.lib().sdq_gemm_ex(cfg._ref, _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
                                           _dev(packed, "packed"), N, K, _dev(Y, "Y"),
                                           _stream(stream), path), "sdq_gemm")
         return Y
     ws = workspace if workspace is not None else torch.empty(ws_bytes, dtype=torch.uint8,
                                                              device=Xq.device)
     _need_bytes(ws, ws_bytes, "workspace")
-    _lib.check(_lib.lib().sdq_gemm_ws(C.byref(cfg.c()), _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
+    _lib.check(_lib.lib().sdq_gemm_ws(cfg._ref, _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
                                       _dev(packed, "packed"), N, K, _dev(Y, "Y"),
                                       _dev(ws, "workspace"), ws.numel() * ws.element_size(),
                                       _stream(stream), path), "sdq_gemm_ws")
@@ -394,13 +436,13 @@ def unpack_weights(packed, N: int, K: int, cfg: Config, workspace=None, stream=N
     expanded B operands in `workspace` (a uint8 CUDA tensor of at least
     gemm_workspace_size(cfg, M, N, K, PATH_DENSE) bytes, or a fresh one),
     which is returned for gemm_unpacked."""
-    import torch
+    torch = _torch()
     _need_bytes(packed, pack_size(cfg, N, K), "packed")
     nb = gemm_workspace_size(cfg, 0, N, K, PATH_DENSE)
     ws = workspace if workspace is not None else torch.empty(nb, dtype=torch.uint8, device=packed.device)
     _need_bytes(ws, nb, "workspace")
     _same_device(packed, ws)
-    _lib.check(_lib.lib().sdq_unpack_weights(C.byref(cfg.c()), _dev(packed, "packed"), N, K,
+    _lib.check(_lib.lib().sdq_unpack_weights(cfg._ref, _dev(packed, "packed"), N, K,
                                              _dev(ws, "workspace"), ws.numel() * ws.element_size(),
                                              _stream(stream)), "sdq_unpack_weights")
     return ws
@@ -410,7 +452,7 @@ def gemm_unpacked(Xq, s_a, packed, N: int, K: int, cfg: Config, workspace, out=N
     """Pass 2 of the two-pass MX path (sdq_gemm_unpacked): Y from the operands
     unpack_weights wrote into `workspace` for the same packed, N and K; equal
     to gemm(..., path=PATH_DENSE) bit for bit."""
-    import torch
+    torch = _torch()
     if Xq.dim() != 2:
         raise ValueError("Xq must be [M, K]")
     M = Xq.shape[0]
@@ -420,7 +462,7 @@ def gemm_unpacked(Xq, s_a, packed, N: int, K: int, cfg: Config, workspace, out=N
     _need_bytes(workspace, gemm_workspace_size(cfg, M, N, K, PATH_DENSE), "workspace")
     Y = _out(out, M, N, cfg, Xq.device)
     _same_device(Xq, s_a, packed, Y, workspace)
-    _lib.check(_lib.lib().sdq_gemm_unpacked(C.byref(cfg.c()), _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
+    _lib.check(_lib.lib().sdq_gemm_unpacked(cfg._ref, _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
                                             _dev(packed, "packed"), N, K, _dev(workspace, "workspace"),
                                             workspace.numel() * workspace.element_size(), _dev(Y, "Y"),
                                             _stream(stream)), "sdq_gemm_unpacked")
@@ -431,7 +473,7 @@ def gemm_static(Xq, s_a, packed, N: int, K: int, cfg: Config, out=None, path: in
                 stream=None):
     """gemm() without a workspace: sdq_gemm_static, whose two-pass path uses the
     library's static 48 MiB scratch array (nothing is allocated by the call)."""
-    import torch
+    torch = _torch()
     if Xq.dim() != 2:
         raise ValueError("Xq must be [M, K]")
     M = Xq.shape[0]
@@ -440,7 +482,7 @@ def gemm_static(Xq, s_a, packed, N: int, K: int, cfg: Config, out=None, path: in
     _need_bytes(packed, pack_size(cfg, N, K), "packed")
     Y = _out(out, M, N, cfg, Xq.device)
     _same_device(Xq, s_a, packed, Y)
-    _lib.check(_lib.lib().sdq_gemm_static(C.byref(cfg.c()), _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
+    _lib.check(_lib.lib().sdq_gemm_static(cfg._ref, _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
                                           _dev(packed, "packed"), N, K, _dev(Y, "Y"),
                                           _stream(stream), path), "sdq_gemm_static")
     return Y
@@ -452,7 +494,7 @@ def linear(X, packed, N: int, K: int, cfg: Config, out=None, xq=None, scales=Non
     kernel on the decode path (sdq_linear); sdq_quantize_act then
     sdq_gemm_ws where the GEMM takes a workspace; otherwise sdq_linear's two
     kernels back to back."""
-    import torch
+    torch = _torch()
     if X.dim() != 2 or X.shape[1] != K:
         raise ValueError(f"X must be [M, {K}], got {list(X.shape)}")
     M = X.shape[0]
@@ -464,13 +506,19 @@ def linear(X, packed, N: int, K: int, cfg: Config, out=None, xq=None, scales=Non
     _need_bytes(packed, pack_size(cfg, N, K), "packed")
     Y = _out(out, M, N, cfg, X.device)
     _same_device(X, Xq, s_a, packed, Y, workspace)
-    if gemm_workspace_size(cfg, M, N, K) > 0:
-        quantize_act(X, cfg, out=Xq, scales=s_a, stream=stream)
-        gemm(Xq, s_a, packed, N, K, cfg, out=Y, stream=stream, workspace=workspace)
-        return Y, Xq, s_a
-    _lib.check(_lib.lib().sdq_linear(C.byref(cfg.c()), _dev(X, "X"), dt, M, _dev(Xq, "Xq"),
-                                     _dev(s_a, "s_a"), _dev(packed, "packed"), N, K, _dev(Y, "Y"),
-                                     _stream(stream)), "sdq_linear")
+    args = (cfg._ref, _dev(X, "X"), dt, M, _dev(Xq, "Xq"), _dev(s_a, "s_a"), _dev(packed, "packed"), N, K,
+            _dev(Y, "Y"))
+    st = _stream(stream)
+    if workspace is not None and workspace.is_cuda and workspace.is_contiguous():
+        rc = _lib.lib().sdq_linear_ws(*args, workspace.data_ptr(), workspace.nbytes, st)
+    else:
+        rc = _lib.lib().sdq_linear_ws(*args, None, 0, st)
+    if rc == _lib.ERR_BUFFER_TOO_SMALL:  # the path takes a workspace and none that serves was given
+        need = gemm_workspace_size(cfg, M, N, K)
+        ws = torch.empty(need, dtype=torch.uint8, device=X.device) if workspace is None else workspace
+        _need_bytes(ws, need, "workspace")
+        rc = _lib.lib().sdq_linear_ws(*args, _dev(ws, "workspace"), ws.nbytes, st)
+    _lib.check(rc, "sdq_linear")
     return Y, Xq, s_a
 
 
@@ -478,7 +526,7 @@ def gemm_path(cfg: Config, M: int, N: int, K: int, workspace: bool = False) -> i
     """The path sdq_gemm takes (or sdq_gemm_ws and sdq_gemm_static, with workspace=True)."""
     p = C.c_int32()
     if workspace:
-        _lib.check(_lib.lib().sdq_gemm_path_ws(C.byref(cfg.c()), M, N, K, C.byref(p)), "sdq_gemm_path_ws")
+        _lib.check(_lib.lib().sdq_gemm_path_ws(cfg._ref, M, N, K, C.byref(p)), "sdq_gemm_path_ws")
     else:
-        _lib.check(_lib.lib().sdq_gemm_path(C.byref(cfg.c()), M, N, K, C.byref(p)), "sdq_gemm_path")
+        _lib.check(_lib.lib().sdq_gemm_path(cfg._ref, M, N, K, C.byref(p)), "sdq_gemm_path")
     return p.value

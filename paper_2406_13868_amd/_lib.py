@@ -13,6 +13,7 @@ STATUS = {
     -4: "SDQ_ERR_BUFFER_TOO_SMALL", -5: "SDQ_ERR_HIP", -6: "SDQ_ERR_UNSUPPORTED",
     -7: "SDQ_ERR_VALUE", -8: "SDQ_ERR_TOO_LARGE",
 }
+ERR_BUFFER_TOO_SMALL = -4
 FAMILY_INT, FAMILY_MX, FAMILY_DUAL = 0, 1, 2
 FMT_INT8, FMT_INT4, FMT_E4M3, FMT_E2M1 = 1, 2, 3, 4
 METRIC_MAGNITUDE, METRIC_PRODUCT = 0, 1
@@ -28,7 +29,7 @@ EXPORTS = (
     "sdq_pack_logical", "sdq_unpack_dense", "sdq_quantize_act", "sdq_gemm", "sdq_gemm_ex",
     "sdq_gemm_path", "sdq_linear", "sdq_gemm_workspace_size", "sdq_gemm_ws",
     "sdq_quantize_act_dual", "sdq_gemm_dual", "sdq_gemm_static", "sdq_gemm_path_ws",
-    "sdq_unpack_weights", "sdq_gemm_unpacked",
+    "sdq_unpack_weights", "sdq_gemm_unpacked", "sdq_linear_ws",
 )
 STATIC_SCRATCH_BYTES = 48 * 1024 * 1024
 
@@ -112,6 +113,7 @@ def lib() -> C.CDLL:
             "sdq_gemm_ws": (C.c_int, [cfgp, vp, vp, i64, vp, i64, i64, vp, vp, C.c_size_t, vp,
                                       C.c_int32]),
             "sdq_linear": (C.c_int, [cfgp, vp, C.c_int32, i64, vp, vp, vp, i64, i64, vp, vp]),
+            "sdq_linear_ws": (C.c_int, [cfgp, vp, C.c_int32, i64, vp, vp, vp, i64, i64, vp, vp, C.c_size_t, vp]),
             "sdq_quantize_act_dual": (C.c_int, [cfgp, vp, C.c_int32, i64, i64, vp, vp, vp, vp, vp]),
             "sdq_gemm_dual": (C.c_int, [cfgp, vp, vp, vp, vp, i64, vp, i64, i64, vp, vp]),
             "sdq_gemm_static": (C.c_int, [cfgp, vp, vp, i64, vp, i64, i64, vp, vp, C.c_int32]),

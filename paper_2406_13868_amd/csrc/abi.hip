@@ -347,6 +347,30 @@ extern "C" sdq_status sdq_linear(const sdq_config* cfg, const void* X, int32_t x
   return sdq_gemm(cfg, Xq, s_a, M, packed, N, K, Y, stream);
 }
 
+extern "C" sdq_status sdq_linear_ws(const sdq_config* cfg, const void* X, int32_t x_dtype, int64_t M,
+                                    void* Xq, float* s_a, const void* packed, int64_t N, int64_t K,
+                                    void* Y, void* workspace, size_t ws_bytes, void* stream) {
+  Cfg c;
+  const sdq_status s = check_config(cfg, N, K, &c);
+  if (s != SDQ_OK) return s;
+  if (M < 0 || M > (int64_t(1) << 31) || M * N > (int64_t(1) << 40)) return SDQ_ERR_SHAPE;
+  if (x_dtype != SDQ_DTYPE_F32 && x_dtype != SDQ_DTYPE_BF16) return SDQ_ERR_CONFIG;
+  if (c.dual) return SDQ_ERR_UNSUPPORTED;
+  const int32_t path = auto_path_ws(c, M, N, K);
+  const size_t need = path_workspace_bytes(c, path, M, N, K);
+  if (need == 0) return sdq_linear(cfg, X, x_dtype, M, Xq, s_a, packed, N, K, Y, stream);
+  if (ws_bytes < need) return SDQ_ERR_BUFFER_TOO_SMALL;
+  // every argument error before the first launch
+  if (!X || !Xq || !s_a || !packed || !Y || !workspace) return SDQ_ERR_NULL;
+  if (reinterpret_cast<uintptr_t>(X) % 16 || reinterpret_cast<uintptr_t>(Xq) % 16 ||
+      reinterpret_cast<uintptr_t>(packed) % 16 || reinterpret_cast<uintptr_t>(workspace) % 16 ||
+      reinterpret_cast<uintptr_t>(Y) % 4)
+    return SDQ_ERR_SHAPE;
+  const sdq_status q = sdq_quantize_act(cfg, X, x_dtype, M, K, Xq, s_a, stream);
+  if (q != SDQ_OK) return q;
+  return sdq_gemm_ws(cfg, Xq, s_a, M, packed, N, K, Y, workspace, ws_bytes, stream, path);
+}
+
 extern "C" sdq_status sdq_quantize_act_dual(const sdq_config* cfg, const void* X, int32_t x_dtype,
                                             int64_t M, int64_t K, void* Xq_o, float* s_a_o,
                                             void* Xq_i, void* e_a_i, void* stream) {

@@ -1,0 +1,45 @@
+"""GPU: sdq.linear (one library call, with or without a workspace) equals
+quantize_act followed by gemm bit for bit on every path sdq_linear_ws can
+take, and refuses a workspace that does not serve."""
+import copy
+import pickle
+
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import say, torch_cuda
+
+import paper_2406_13868_amd as sdq
+
+pytestmark = pytest.mark.gpu
+INT, MX = sdq.Config.int_family(), sdq.Config.mx_family()
+
+
+@pytest.mark.parametrize("cfg,M,N,K", [(INT, 1, 256, 512), (INT, 16, 256, 512), (INT, 64, 8192, 256),
+                                       (INT, 33, 96, 8192), (MX, 1, 96, 256), (MX, 5, 96, 1024),
+                                       (MX, 600, 10240, 256)])
+def test_linear_equals_quantize_then_gemm(cfg, M, N, K):
+    torch = torch_cuda()
+    say("linear ws", cfg.label, M, N, K)
+    X = torch.from_numpy(synth.make_x(2, M, K)).cuda()
+    blob = torch.from_numpy(sdq.pack(synth.make_w(2, 0, N, K), cfg)).cuda()
+    Xq, s_a = sdq.quantize_act(X, cfg)
+    Y = sdq.gemm(Xq, s_a, blob, N, K, cfg)
+    nb = sdq.gemm_workspace_size(cfg, M, N, K)
+    for ws in (None, torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda")):
+        Y2, Xq2, s2 = sdq.linear(X, blob, N, K, cfg, workspace=ws)
+        assert torch.equal(Xq, Xq2) and torch.equal(s_a, s2)
+        fused = nb == 0 and sdq.gemm_path(cfg, M, N, K) == sdq.PATH_DECODE
+        assert torch.equal(Y, Y2), "fused" if fused else "two calls"
+    if nb:
+        with pytest.raises(ValueError, match="workspace holds"):
+            sdq.linear(X, blob, N, K, cfg, workspace=torch.empty(nb - 16, dtype=torch.uint8, device="cuda"))
+
+
+def test_a_used_config_copies_and_pickles():
+    cfg = sdq.Config.int_family()
+    assert sdq.pack_size(cfg, 64, 256) == sdq.pack_size(cfg, 64, 256)
+    for other in (copy.deepcopy(cfg), pickle.loads(pickle.dumps(cfg))):
+        assert other == cfg and hash(other) == hash(cfg) and sdq.pack_size(other, 64, 256) == sdq.pack_size(cfg, 64, 256)
+    assert np.array_equal(sdq.pack(synth.make_w(2, 0, 64, 256), other), sdq.pack(synth.make_w(2, 0, 64, 256), cfg))

@@ -129,20 +129,6 @@ __device__ __forceinline__ v4i outlier_bytes_np(const uint32_t (&hw)[NP]) {
 __device__ __forceinline__ int swz_o(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 __device__ __forceinline__ int swz_i(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
 
-// Y[idx .. idx + 3] = v through the resource of out_rows (Y 16-byte aligned and
-// N a multiple of 4, so that the four share a row).
-__device__ __forceinline__ void store_out4(const OutRows& y, uint32_t idx, float4 v) {
-  if (y.bf16) {
-    typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-    const u2v q = {uint32_t(bf16_bits(v.x)) | (uint32_t(bf16_bits(v.y)) << 16),
-                   uint32_t(bf16_bits(v.z)) | (uint32_t(bf16_bits(v.w)) << 16)};
-    __builtin_amdgcn_raw_buffer_store_b64(q, y.r, idx * 2u, 0, 0);
-  } else {
-    const v4i q = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(q, y.r, idx * 4u, 0, 0);
-  }
-}
-
 template <int MS, int TN, int NP, int KG>
 __global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(DualArgs a) {
   constexpr int BM = 32 * MS;
@@ -492,34 +478,12 @@ __global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(
   if (wave8 < kDWaves) run(std::integral_constant<int, 0>{});
   else run(std::integral_constant<int, 1>{});
 
-  // ---- the waves that share an output group store an equal part of its tokens.  A request that
-  //      touches many rows of Y costs by the row (four cycles each), so a
-  //      wave stores whole lines of a few rows.
+  // ---- the waves that share an output group store an equal part of its tokens
   const int nw = t0 * kTileN, n_left = a.N - nw;  // the group's outputs
-  const OutRows yr = out_rows(a.Y, a.y_bf16, a.M, a.N, m0, BM);
   constexpr int kRows = BM / (2 * KG);
   const int r_lo = (2 * kg + (wave8 >> 2)) * kRows;
-  if (a.y_vec) {  // four outputs a lane, 256 / kOutW tokens a request
-    constexpr int kL = kOutW / 4;  // lanes per token
-    const int n = 4 * (lane % kL);
-#pragma unroll 8
-    for (int r = r_lo; r < r_lo + kRows; r += 64 / kL) {
-      const float4 v = *reinterpret_cast<const float4*>(&os[(r + lane / kL) * kOutRow + n]);
-      if (n < n_left) store_out4(yr, uint32_t(r + lane / kL) * uint32_t(a.N) + uint32_t(nw + n), v);
-    }
-  } else {
-    const int n = lane % kOutW;
-#pragma unroll 4
-    for (int r = r_lo; r < r_lo + kRows; r += 64 / kOutW) {
-      const int row = r + lane / kOutW;
-      const float v = os[row * kOutRow + n];
-      if (n < n_left) {
-        const uint32_t idx = uint32_t(row) * uint32_t(a.N) + uint32_t(nw + n);
-        if (yr.bf16) __builtin_amdgcn_raw_buffer_store_b16(bf16_bits(v), yr.r, idx * 2u, 0, 0);
-        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), yr.r, idx * 4u, 0, 0);
-      }
-    }
-  }
+  store_staged<kOutW>(os + r_lo * kOutRow, out_rows(a.Y, a.y_bf16, a.M, a.N, m0, BM), a.y_vec, a.N, r_lo, kRows, nw,
+                      n_left, lane);
 }
 
 // Split-K form for few tokens (up to 32, more on narrow layers): one 32-row tile per workgroup, its
@@ -693,7 +657,7 @@ hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, c
   DualArgs a{Xo, s_a, Xi, Ea, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles),
              L.out_off, L.scale_off, L.rows_off};
   a.y_bf16 = c.y_bf16;
-  a.y_vec = N % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
+  a.y_vec = out_vec(Y, N);
   if (dual_decode_fits(M, N, K)) return launch_dual_decode(c, Xo, s_a, Xi, Ea, M, blob, N, K, Y, st);
   return L.out_planes == 2 ? launch_np<2>(a, st) : launch_np<1>(a, st);
 }

@@ -3,14 +3,12 @@
 //
 // gfx950 has no matrix instruction that applies a scale every 16 K, which is
 // what the fp16 inlier scales need, and none that multiplies int8 by fp8.
-// Both branches therefore run on v_mfma_f32_32x32x16_f16, which is exact
+// Both branches therefore run on the f16 matrix instructions, which are exact
 // here: int8 activations, int4 inliers and int8/e4m3 outliers are all exact
-// fp16 numbers, their products are exact in fp32, and a 16-K sum of int8 x
-// int4 products stays below 2^24.
-//   inlier:  P = Xq_blk * q_blk (one MFMA per 16-K block, K = 16 = one scale
-//            block), acc += P * s_blk  (fp32, per column scale)
-//   outlier: acc_o += Xq_blk * q_o_blk (MFMA accumulation), scaled by the
-//            per-row s_o once at the end
+// fp16 numbers, and their products are exact in fp32.
+//   inlier:  the block's fp16 scale times the int4 code travels inside two
+//            fp16 fragments, hi and lo (int_frag.h): acc += hi a + lo a;
+//   outlier: acc_o += q_o a, scaled by the per-row s_o once at the end
 //   Y = s_a * (acc + s_o * acc_o)
 //
 // Tiling: a workgroup of 4 waves owns 4 row tiles of W (128 outputs) and BM
@@ -19,8 +17,21 @@
 // spilling).  Each 128-K chunk of activations is converted from int8 to
 // fp16 and staged in LDS (double buffered) for all 4 waves; each wave streams
 // its own tile's group words (32 bytes per lane per chunk) and
-// expands them in registers into dense fp16 B fragments: lane l holds column
-// l%32 and the 8-group 2*kb + l/32 of every 16-K block kb.
+// expands them in registers into fp16 fragments: lane l holds row l%32 of the
+// tile and the 8-group 2*kb + l/32 of every 16-K block kb.
+//
+// W is the first operand and tokens are the columns, because the outliers run
+// on v_smfmac_f32_32x32x32_f16, whose first operand is the sparse one: one
+// outlier in eight fits its two stored of every four, and it covers 32 K in
+// the time of the dense instruction's 16, so a product costs 2.5 dense f16
+// instructions instead of 3 (1.5 instead of 2 with one-byte scales).
+//
+// What bounds it: matrix time (80 instructions per chunk and wave, and f16
+// ones sustain 1.75 PF) with 440 vector instructions beside it.  The
+// expansion of a word runs under the products of the word before; before
+// that, and with the dense outlier instruction, both waves of a SIMD often
+// expanded at the same time.  4096x4096 at M = 2048 / 4096: 169 / 303 -> 140 /
+// 259 us; 11008x4096 at M = 1024: 233 -> 195.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,6 +66,8 @@ struct MfmaArgs {
   // kc_range) of every tile, raw partial sums to part[z][M][N]
   int k_ranges = 1, kc_range = 0;
   float* part = nullptr;
+  int groups = 1, m_blocks = 1;  // tiled kernel: the grid is 1-D over (K range, tile group, token block)
+  bool y_vec = false;  // four outputs per store (part, or else Y, allows it)
 };
 
 template <int MS, int NI, bool OUT_INT8, int SF>
@@ -68,66 +81,72 @@ __global__ __launch_bounds__(kThreads, 2) void int_mfma_kernel(MfmaArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: chunk offsets stay scalar
   const int col = lane & 31, h = lane >> 5;
-  const int m0 = blockIdx.y * BM;
-  const int tile = blockIdx.x * kWaves + wave;
+  const int items = a.groups * a.m_blocks, range = int(blockIdx.x) / items;
+  int group, mblock;
+  square_work(int(blockIdx.x) - range * items, a.groups, a.m_blocks, group, mblock);
+  const int m0 = mblock * BM;
+  const int tile = group * kWaves + wave;
   const bool tile_ok = tile < a.n_tiles;
   const int KC = a.n_chunks;
-  const int cb = int(blockIdx.z) * a.kc_range;                   // this workgroup's chunks [cb, ce)
+  const int cb = range * a.kc_range;                   // this workgroup's chunks [cb, ce)
   const int ce = a.k_ranges > 1 ? min(KC, cb + a.kc_range) : KC;
 
   // ---- activation staging: BM rows x 128 int8 -> fp16 in LDS
-  // thread -> (row, 16-byte column piece): 8 pieces per row
-  constexpr int kPieces = BM * 8;
-  constexpr int kPerThread = (kPieces + kThreads - 1) / kThreads;
-  uint4 xr[kPerThread];
+  // thread -> (row, 16-byte column piece): 8 pieces per row, piece i of a
+  // thread 32 rows after piece i - 1
+  constexpr int kPerThread = MS;
+  static_assert(BM * 8 == kPerThread * kThreads, "whole pieces per thread");
+  typedef unsigned int u4_ __attribute__((ext_vector_type(4)));
+  u4_ xr[kPerThread];
   // the block's rows through a buffer resource: rows past M, and the bytes of
   // a last partial chunk past the end of the tensor, read 0
   const __amdgpu_buffer_rsrc_t x_rsrc =
       buffer_rsrc(a.Xq + size_t(m0) * a.K, uint32_t(min(a.M - m0, BM)) * uint32_t(a.K));
-  auto load_x = [&](int c) {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int pc = tid + i * kThreads;
-      const int rr = pc >> 3, cp = pc & 7;
-      xr[i] = make_uint4(0, 0, 0, 0);
-      if (pc < kPieces) {
-        typedef unsigned int u4_ __attribute__((ext_vector_type(4)));
-        const u4_ q = __builtin_bit_cast(u4_, __builtin_amdgcn_raw_buffer_load_b128(
-            x_rsrc, uint32_t(rr) * uint32_t(a.K) + uint32_t(cp) * 16u, uint32_t(c) * kChunkK, 0));
-        xr[i] = make_uint4(q[0], q[1], q[2], q[3]);
-      }
-    }
+  const uint32_t xsrc = uint32_t(tid >> 3) * uint32_t(a.K) + uint32_t(tid & 7) * 16u;
+  const int xdst = (tid >> 3) * kLdsRow + (tid & 7) * 16;
+  auto load_x1 = [&](int c, int i) __attribute__((always_inline)) {
+    xr[i] = __builtin_bit_cast(u4_, __builtin_amdgcn_raw_buffer_load_b128(
+                                        x_rsrc, xsrc + uint32_t(i) * 32 * uint32_t(a.K), uint32_t(c) * kChunkK, 0));
   };
-  auto store_x = [&](int buf) {
+  auto store_x1 = [&](int buf, int i) __attribute__((always_inline)) {
+    uint32_t o[8];
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int pc = tid + i * kThreads;
-      if (pc >= kPieces) continue;
-      const int rr = pc >> 3, cp = pc & 7;
-      uint32_t o[8];
-      i8x4_to_f16x4(xr[i].x, o[0], o[1]);
-      i8x4_to_f16x4(xr[i].y, o[2], o[3]);
-      i8x4_to_f16x4(xr[i].z, o[4], o[5]);
-      i8x4_to_f16x4(xr[i].w, o[6], o[7]);
-      uint4* dst = reinterpret_cast<uint4*>(&xs[buf][rr * kLdsRow + cp * 16]);
-      dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
-      dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
-    }
+    for (int q = 0; q < 4; ++q) i8x4_to_f16x4(xr[i][q], o[2 * q], o[2 * q + 1]);
+    uint4* dst = reinterpret_cast<uint4*>(&xs[buf][xdst + i * 32 * kLdsRow]);
+    dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
+    dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
   };
 
   // ---- weight stream of this wave's tile
   // lane (col, h): the 32 bytes at ((h*32 + col)*2 + j)*16, j = 0, 1
-  const uint8_t* wbase = a.blob + size_t(tile_ok ? tile : 0) * KC * kWordBytesPerTC + size_t(lane) * 32;
-  const uint8_t* sbase = a.blob + a.scales_off + size_t(tile_ok ? tile : 0) * KC * kSB + col * a.srow;
-  uint4 wr0, wr1, sr;
-  auto load_w = [&](int c) {
-    if (tile_ok) {
-      wr0 = *reinterpret_cast<const uint4*>(wbase + size_t(c) * kWordBytesPerTC);
-      wr1 = *reinterpret_cast<const uint4*>(wbase + size_t(c) * kWordBytesPerTC + 16);
-      sr = load_row_scales_chunk(sbase + size_t(c) * kSB, a.srow);
+  const int t_ld = min(tile, a.n_tiles - 1);  // spare waves recompute the last tile
+  const __amdgpu_buffer_rsrc_t w_rsrc =
+      buffer_rsrc(a.blob + size_t(t_ld) * KC * kWordBytesPerTC, uint32_t(KC) * kWordBytesPerTC);
+  // the row's scales of a chunk as the low a.srow bytes of one 16-byte
+  // request whatever their format (a load per format would be a branch, whose
+  // join waits for it); what is read beyond them is the next rows' scales or
+  // the row scales that follow in the blob
+  const __amdgpu_buffer_rsrc_t s_rsrc =
+      buffer_rsrc(a.blob + a.scales_off + size_t(t_ld) * KC * kSB, uint32_t(KC) * kSB + 16);
+  const uint32_t soff = uint32_t(col * a.srow) & ~3u, sshift = 8 * (uint32_t(col * a.srow) & 3u);
+  u4_ wr0, wr1, sr;
+  auto load_w = [&](int c) __attribute__((always_inline)) {
+    wr0 = __builtin_bit_cast(u4_, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, uint32_t(lane) * 32, uint32_t(c) * kWordBytesPerTC, 0));
+    wr1 = __builtin_bit_cast(u4_, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, uint32_t(lane) * 32 + 16, uint32_t(c) * kWordBytesPerTC, 0));
+    sr = __builtin_bit_cast(u4_, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, soff, uint32_t(c) * kSB, 0));
+  };
+  // inlier fragments of one group word: hi and lo, or one where an int4 code
+  // times an e4m3 (e6m2) scale has at most 7 (6) significant bits, exact in fp16
+  struct BFrag { h8 h, l; };
+  auto expand = [&](uint32_t w, _Float16 s) __attribute__((always_inline)) {
+    BFrag f;
+    if constexpr (ONE) {
+      const h8 sv8 = {s, s, s, s, s, s, s, s};
+      f.h = inlier_f16<NI>(w) * sv8;
     } else {
-      wr0 = wr1 = sr = make_uint4(0, 0, 0, 0);
+      scaled_hi_lo(inlier_f16<NI>(w), s, f.h, f.l);
     }
+    return f;
   };
 
   f16v acc[MS], acco[MS];
@@ -136,72 +155,122 @@ __global__ __launch_bounds__(kThreads, 2) void int_mfma_kernel(MfmaArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) { acc[s][e] = 0.f; acco[s][e] = 0.f; }
 
-  load_x(cb);
+  const int last = ce - 1;
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) load_x1(cb, i);
   load_w(cb);
-  store_x(0);
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) {
+    store_x1(0, i);
+    load_x1(min(cb + 1, last), i);
+  }
   __syncthreads();
+  const uint32_t arow = uint32_t(col * kLdsRow + h * 8);
+  h8 a0[MS], a1[MS];
+  auto read_a = [&](h8 (&av)[MS], int buf, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+      av[ms] = *reinterpret_cast<const h8*>(&xs[buf][arow + ms * 32 * kLdsRow + kb * 16]);
+  };
+  auto inlier = [&](const BFrag& f, const h8 (&av)[MS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms) acc[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.h, av[ms], acc[ms], 0, 0, 0);
+    if constexpr (!ONE) {
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms) acc[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.l, av[ms], acc[ms], 0, 0, 0);
+    }
+  };
+  BFrag f0, f1;
+  {
+    const uint32_t sv[4] = {sr.x >> sshift, sr.y, sr.z, sr.w};
+    f0 = expand(wr0.x, block_scale<SF>(sv, 0, a.qs));
+  }
+  read_a(a0, 0, 0);
 
+  // A pair of 16-K blocks is three blocks of matrix instructions: the first
+  // word's inliers, both words' outliers (one sparse instruction over 32 K),
+  // the second word's inliers.  While a block runs, the vector unit expands
+  // the next word, and a0 / a1 are read as soon as their last use is over.
+  // The activations of chunk c + 1 go to LDS a quarter per pair, their
+  // registers taking chunk c + 2's.
   for (int c = cb; c < ce; ++c) {
     const int buf = (c - cb) & 1;
     const uint32_t wv[8] = {wr0.x, wr0.y, wr0.z, wr0.w, wr1.x, wr1.y, wr1.z, wr1.w};
-    const uint32_t sv[4] = {sr.x, sr.y, sr.z, sr.w};
-    if (c + 1 < ce) { load_x(c + 1); load_w(c + 1); }
+    const uint32_t sv[4] = {sr.x >> sshift, sr.y, sr.z, sr.w};
+    load_w(min(c + 1, last));
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-      const _Float16 s = block_scale<SF>(sv, kb, a.qs);
-      h8 bh, bl;
-      if constexpr (ONE) {
-        // an int4 code times an e4m3 (e6m2) scale has at most 7 (6)
-        // significant bits: exact in fp16, so one fragment carries it
-        const h8 sv8 = {s, s, s, s, s, s, s, s};
-        bh = inlier_f16<NI>(wv[kb]) * sv8;
+    for (int kp = 0; kp < 4; ++kp) {
+      read_a(a1, buf, 2 * kp + 1);
+      f1 = expand(wv[2 * kp + 1], block_scale<SF>(sv, 2 * kp + 1, a.qs));
+      // lane half 0 takes the first groups of both halves' words (blocks 2 kp
+      // and 2 kp + 1), half 1 the second
+      const auto ws = __builtin_amdgcn_permlane32_swap(wv[2 * kp], wv[2 * kp + 1], false, false);
+      const SparseF16 bo = sparse_outliers_f16<OUT_INT8>(ws[0], ws[1]);
+      inlier(f0, a0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms) {
+        const h16 a2 = __builtin_shufflevector(a0[ms], a1[ms], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+        acco[ms] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(bo.v, a2, acco[ms], bo.idx, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (kp < 3) {
+        read_a(a0, buf, 2 * kp + 2);
+        f0 = expand(wv[2 * kp + 2], block_scale<SF>(sv, 2 * kp + 2, a.qs));
       } else {
-        scaled_hi_lo(inlier_f16<NI>(wv[kb]), s, bh, bl);
+        const uint32_t svn[4] = {sr.x >> sshift, sr.y, sr.z, sr.w};
+        f0 = expand(wr0.x, block_scale<SF>(svn, 0, a.qs));  // chunk c + 1's first word
       }
-      const h8 bo = outlier_f16<OUT_INT8>(wv[kb]);
-      h8 av[MS];
-#pragma unroll
-      for (int ms = 0; ms < MS; ++ms)
-        av[ms] = *reinterpret_cast<const h8*>(&xs[buf][(ms * 32 + col) * kLdsRow + kb * 16 + h * 8]);
-#pragma unroll
-      for (int ms = 0; ms < MS; ++ms) acc[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[ms], bh, acc[ms], 0, 0, 0);
-#pragma unroll
-      for (int ms = 0; ms < MS; ++ms) acco[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[ms], bo, acco[ms], 0, 0, 0);
-      if constexpr (!ONE) {
-#pragma unroll
-        for (int ms = 0; ms < MS; ++ms) acc[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[ms], bl, acc[ms], 0, 0, 0);
+      if (kp < kPerThread) {
+        store_x1(buf ^ 1, kp);
+        load_x1(min(c + 2, last), kp);
       }
+      inlier(f1, a1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (c + 1 < ce) {
-      store_x(buf ^ 1);
-      __syncthreads();
-    }
+    __syncthreads();
+    read_a(a0, buf ^ 1, 0);
   }
 
+  // ---- lane (col, h) holds token m0 + 32 ms + col, outputs 8 j + 4 h .. + 3
+  //      of the tile; each wave stages 32 tokens at a time in its own LDS
+  __syncthreads();
   if (!tile_ok) return;
-  const int n = tile * kTileN + col;
-  if (n >= a.N) return;
-  const float so = reinterpret_cast<const float*>(a.blob + a.rows_off)[n];
+  const int n0 = tile * kTileN;
+  float* const os = reinterpret_cast<float*>(&xs[0][0]) + wave * (32 * (kTileN + 4));
+  const float* const sop = reinterpret_cast<const float*>(a.blob + a.rows_off) + n0 + 4 * h;
   // the inlier row scale of two-level e4m3 scales (a power of two: exact)
-  const float gi = SC8 ? reinterpret_cast<const float*>(a.blob + a.irow_off)[n] : 1.f;
-  if (a.part) {
-    // this K range's partial sums; split_reduce adds the ranges in order and
-    // scales by s_a
-    const OutRows pr = out_rows(a.part + size_t(blockIdx.z) * size_t(a.M) * size_t(a.N), false, a.M, a.N, m0,
-                                32 * MS);
+  const float* const gip = reinterpret_cast<const float*>(a.blob + (SC8 ? a.irow_off : a.rows_off)) + n0 + 4 * h;
+  float4 so[4], gi[4];
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) store_out(pr, a.N, n, ms, e, h, fmaf(so, acco[ms][e], gi * acc[ms][e]));
-    return;
+  for (int j = 0; j < 4; ++j) {
+    so[j] = *reinterpret_cast<const float4*>(sop + 8 * j);
+    gi[j] = SC8 ? *reinterpret_cast<const float4*>(gip + 8 * j) : make_float4(1.f, 1.f, 1.f, 1.f);
   }
-  const RowScales<MS> rs = load_row_scales<MS>(a.s_a, a.M, m0, h);
-  const OutRows yr = out_rows(a.Y, a.y_bf16, a.M, a.N, m0, 32 * MS);
+  // with K ranges, this range's partial sums; split_reduce adds the ranges in
+  // order and scales by s_a
+  const OutRows yr = a.part ? out_rows(a.part + size_t(range) * size_t(a.M) * size_t(a.N), false, a.M, a.N, m0, BM)
+                            : out_rows(a.Y, a.y_bf16, a.M, a.N, m0, BM);
+  const __amdgpu_buffer_rsrc_t sr_rsrc = buffer_rsrc(a.s_a + m0, uint32_t(min(a.M - m0, BM)) * 4u);
+  float sa[MS];
 #pragma unroll
   for (int ms = 0; ms < MS; ++ms)
+    sa[ms] = a.part ? 1.f
+                    : __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sr_rsrc, uint32_t(ms * 32 + col) * 4u, 0, 0));
 #pragma unroll
-    for (int e = 0; e < 16; ++e)
-      store_out(yr, a.N, n, ms, e, h, rs.v[ms][e] * fmaf(so, acco[ms][e], gi * acc[ms][e]));
+  for (int ms = 0; ms < MS; ++ms) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float qs[4] = {so[j].x, so[j].y, so[j].z, so[j].w}, qg[4] = {gi[j].x, gi[j].y, gi[j].z, gi[j].w};
+      float v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = sa[ms] * fmaf(qs[i], acco[ms][4 * j + i], qg[i] * acc[ms][4 * j + i]);
+      *reinterpret_cast<float4*>(&os[col * (kTileN + 4) + 8 * j + 4 * h]) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    store_staged<kTileN>(os, yr, a.y_vec, a.N, ms * 32, 32, n0, a.N - n0, lane);
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // Split-K form for few tokens (M <= 64): one 32-row tile of W per workgroup,
@@ -430,13 +499,16 @@ hipError_t launch_ms_ni(const Cfg& c, const MfmaArgs& a, hipStream_t st) {
     if (waves4 >= 2048 || a.n_chunks < 16) return launch_splitk<MS, NI, 4, SF>(c, a, st);
     return launch_splitk<MS, NI, 8, SF>(c, a, st);
   } else {
-    const dim3 grid(unsigned((a.n_tiles + kWaves - 1) / kWaves), unsigned((a.M + 32 * MS - 1) / (32 * MS)),
-                    unsigned(a.k_ranges));
+    MfmaArgs b = a;
+    b.groups = (a.n_tiles + kWaves - 1) / kWaves;
+    b.m_blocks = (a.M + 32 * MS - 1) / (32 * MS);
+    b.y_vec = a.part ? a.N % 4 == 0 : out_vec(a.Y, a.N);
+    const dim3 grid(unsigned(b.groups) * unsigned(b.m_blocks) * unsigned(b.k_ranges));
     const dim3 block(kThreads);
     if (c.fmt_o == SDQ_FMT_INT8)
-      hipLaunchKernelGGL((int_mfma_kernel<MS, NI, true, SF>), grid, block, 0, st, a);
+      hipLaunchKernelGGL((int_mfma_kernel<MS, NI, true, SF>), grid, block, 0, st, b);
     else
-      hipLaunchKernelGGL((int_mfma_kernel<MS, NI, false, SF>), grid, block, 0, st, a);
+      hipLaunchKernelGGL((int_mfma_kernel<MS, NI, false, SF>), grid, block, 0, st, b);
     return hipGetLastError();
   }
 }

@@ -13,6 +13,7 @@ namespace sdq {
 namespace intfrag {
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h16 __attribute__((ext_vector_type(16)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
@@ -127,6 +128,39 @@ __device__ __forceinline__ h8 outlier_f16(uint32_t w) {
   const uint32_t vlo = uint32_t(v), vhi = uint32_t(v >> 32);
   const u4v out = {upper ? 0u : vlo, upper ? 0u : vhi, upper ? vlo : 0u, upper ? vhi : 0u};
   return __builtin_bit_cast(h8, out);
+}
+
+// Sparse fp16 outlier operand of v_smfmac_f32_32x32x32_f16 for two group words
+// (that instruction stores two of every four positions, each with a 2-bit
+// index, and multiplies 32 dense K in the time the dense one takes for 16).
+// The outlier of a group at position p goes to slot p >> 1 of the group's
+// four: slots 0 and 2 hold positions {0, 1} of their four and slots 1 and 3
+// {2, 3}, so the two positions of a four ascend; an empty slot has value 0 at
+// position 0 or 2.  v: two dwords per group; idx: a byte per group.
+struct SparseF16 {
+  h8 v;
+  int idx;
+};
+template <bool OUT_INT8>
+__device__ __forceinline__ SparseF16 sparse_outliers_f16(uint32_t wa, uint32_t wb) {
+  // index byte of position p: 0x88 with bit (p & 1) << (p & 6) set
+  constexpr uint32_t kIdxLo = 0x8C888988u, kIdxHi = 0xC8889888u;
+  uint32_t p[2];
+  uint64_t v[2];
+  const uint32_t w[2] = {wa, wb};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float f;
+    if constexpr (OUT_INT8) f = (float)(int(w[i]) >> 24);
+    else f = __builtin_amdgcn_cvt_f32_fp8(int(w[i]), 3);
+    const uint32_t hb = uint32_t(__builtin_bit_cast(unsigned short, (_Float16)f));
+    const uint32_t prod = __umul24(w[i] & 0x00080808u, kOutPosMagic);  // the position in bits 24-26
+    p[i] = __builtin_amdgcn_ubfe(prod, 24, 3);
+    v[i] = uint64_t(hb) << ((prod >> 21) & 0x30u);  // 16 * (p >> 1)
+  }
+  const uint32_t sel = ((p[1] << 8) | p[0]) | 0x0C0C0000u;
+  const u4v d = {uint32_t(v[0]), uint32_t(v[0] >> 32), uint32_t(v[1]), uint32_t(v[1] >> 32)};
+  return {__builtin_bit_cast(h8, d), int(__builtin_amdgcn_perm(kIdxHi, kIdxLo, sel))};
 }
 
 // Dense int8 outlier bytes of one group word (position p at byte p of lo:hi).

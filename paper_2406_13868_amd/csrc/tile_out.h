@@ -75,6 +75,55 @@ __device__ __forceinline__ void store_out(const OutRows& y, int N, int n, int ms
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), y.r, idx * 4u, 0, 0);
 }
 
+// Y[idx .. idx + 3] = v through the resource of out_rows (Y 16-byte aligned and
+// N a multiple of 4, so that the four share a row).
+__device__ __forceinline__ void store_out4(const OutRows& y, uint32_t idx, float4 v) {
+  typedef int i4v_ __attribute__((ext_vector_type(4)));
+  typedef uint32_t u2v_ __attribute__((ext_vector_type(2)));
+  if (y.bf16) {
+    const u2v_ q = {uint32_t(bf16_bits(v.x)) | (uint32_t(bf16_bits(v.y)) << 16),
+                    uint32_t(bf16_bits(v.z)) | (uint32_t(bf16_bits(v.w)) << 16)};
+    __builtin_amdgcn_raw_buffer_store_b64(q, y.r, idx * 2u, 0, 0);
+  } else {
+    const i4v_ q = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(q, y.r, idx * 4u, 0, 0);
+  }
+}
+inline bool out_vec(const void* Y, int64_t N) { return N % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0; }
+
+// One wave stores `rows` tokens of W outputs from LDS (os: W + 4 floats per
+// token) to the rows r0 .. of y and the columns n0 .. n0 + min(W, n_left).
+// Where the tokens are the columns of the matrix instruction, a lane holds
+// four outputs of one token, and stored from there a request would touch 32
+// rows of Y (it costs about four cycles a row); staged in LDS, a request
+// covers whole lines of a few rows.
+template <int W>
+__device__ __forceinline__ void store_staged(const float* os, const OutRows& y, bool vec, int N, int r0, int rows,
+                                             int n0, int n_left, int lane) {
+  constexpr int kRow = W + 4;
+  if (vec) {  // four outputs a lane
+    constexpr int kL = W / 4;  // lanes per token
+    const int n = 4 * (lane % kL);
+#pragma unroll 8
+    for (int r = 0; r < rows; r += 64 / kL) {
+      const float4 v = *reinterpret_cast<const float4*>(&os[(r + lane / kL) * kRow + n]);
+      if (n < n_left) store_out4(y, uint32_t(r0 + r + lane / kL) * uint32_t(N) + uint32_t(n0 + n), v);
+    }
+  } else {
+    const int n = lane % W;
+#pragma unroll 4
+    for (int r = 0; r < rows; r += 64 / W) {
+      const int row = r + lane / W;
+      const float v = os[row * kRow + n];
+      if (n < n_left) {
+        const uint32_t idx = uint32_t(r0 + row) * uint32_t(N) + uint32_t(n0 + n);
+        if (y.bf16) __builtin_amdgcn_raw_buffer_store_b16(bf16_bits(v), y.r, idx * 2u, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), y.r, idx * 4u, 0, 0);
+      }
+    }
+  }
+}
+
 // Y[i] = v for a plain element index (fp32 or bf16 elements).
 __device__ __forceinline__ void store_y(void* Y, bool bf16, size_t i, float v) {
   if (bf16)

@@ -49,7 +49,13 @@ int32_t auto_path(const Cfg& c, int64_t M, int64_t K) {
 // 81.1 / 86.1; 4096x11008 at M = 512 / 1024: 108 / 192 against 138 / 218;
 // 11008x4096 at M = 512 (344 workgroups): 118 against 135.  On fuller grids
 // it loses (11008x4096 at M = 640 / 768: 147 / 208 against 140 / 200).
-bool split_wins(int64_t M, int64_t N, int64_t K) {
+//
+// Up to 16 tokens, and wherever one round of its workgroups holds the grid,
+// the small-M kernel of the matrix-core path is the faster one until rows
+// are very long (4096x11008 at M = 16 / 32: 16.9 / 21.5 us against 20.7 / 21.8;
+// 4096x16384 with int8 outliers at M = 16: 23.9 against 23.6).
+bool split_wins(const Cfg& c, int64_t M, int64_t N, int64_t K) {
+  if (M <= 64 && K < 16384 && int_small_wins(c, M, N)) return false;
   if (M > kSplitMaxM) return K >= 1024 && (N + 127) / 128 * ((M + 127) / 128) < 384;
   return K >= 8192 || (M >= 64 && N >= 8192) || M >= 256;
 }
@@ -71,7 +77,7 @@ int32_t auto_path_ws(const Cfg& c, int64_t M, int64_t N, int64_t K) {
   if (c.mx && c.n_o > 0 && M >= kDenseMinM && wgs >= 160) return SDQ_PATH_DENSE;
   if (c.mx && mx_split_wins(M, N, K)) return SDQ_PATH_SPLITK;
   const int32_t p = auto_path(c, M, K);
-  if (!c.mx && p == SDQ_PATH_MFMA && split_wins(M, N, K)) return SDQ_PATH_SPLITK;
+  if (!c.mx && p == SDQ_PATH_MFMA && split_wins(c, M, N, K)) return SDQ_PATH_SPLITK;
   return p;
 }
 

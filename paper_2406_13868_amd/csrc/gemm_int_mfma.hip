@@ -578,6 +578,7 @@ hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, in
   a.y_bf16 = c.y_bf16;
   a.qs = c.qv == 64 ? 2 : c.qv == 32 ? 1 : 0;
   a.srow = (kChunkK / c.qv) * c.scale_bytes();
+  if (int_small_wins(c, M, N)) return launch_int_small(c, Xq, s_a, M, blob, N, K, Y, st);
   if (M <= 32) return launch_ms<1>(c, a, st);
   // 33..64 tokens: one 64-token block expands every weight once; when that
   // leaves fewer workgroups than compute units, two 32-token blocks fill the

@@ -85,6 +85,11 @@ bool decode_fused_fits(int64_t M, int64_t K);
 hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                            const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st);
 
+// INT family, few tokens (any M; 16 or 32 tokens per workgroup).
+bool int_small_wins(const Cfg& c, int64_t M, int64_t N);
+hipError_t launch_int_small(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M, const uint8_t* blob,
+                            int64_t N, int64_t K, void* Y, hipStream_t st);
+
 // INT family, matrix-core kernel with K split across workgroups (tens to a
 // few hundred tokens): partial sums of the K ranges in `workspace` (at least
 // int_split_workspace_bytes(M, N, K) bytes, 16-byte aligned), then a second

@@ -60,14 +60,15 @@ bool split_wins(const Cfg& c, int64_t M, int64_t N, int64_t K) {
   return K >= 8192 || (M >= 64 && N >= 8192) || M >= 256;
 }
 
-// The MX family's split-K path where the one-pass grid of 128 outputs x 128
-// tokens per workgroup would hold at most 128 workgroups (half the CUs):
-// measured on the LLaMA-7B shapes, 4096x4096 takes 9.1 / 14.3 / 20.8 us at M
-// = 1 / 64 / 128 against 25.9 / 29.8 / 26.5 in one pass, and 28.6 against 30.8
-// at 512; 4096x11008 14.1 / 19.7 / 34.8 / 51.4 at M = 1 / 64 / 256 / 512
-// against 63.1 / 72.4 / 64.7 / 73.9.  It loses on fuller grids (11008x4096
-// at M = 256: 40.5 against 39.6; 4096x4096 at M = 768: 41.5 against 38.6),
-// and needs K for at least two ranges.
+// The MX family's split-K path (up to a few hundred tokens the kernel that
+// splits K over the waves of a workgroup, else K ranges and a second pass)
+// where the one-pass grid of 128 outputs x 128 tokens per workgroup would hold
+// at most 128 workgroups (half the CUs): measured on the LLaMA-7B shapes,
+// 4096x4096 takes 4.9 / 7.7 / 13.9 us at M = 1 / 64 / 128 against 25.4 / 29.4
+// / 26.5 in one pass, and 28.4 against 30.8 at 512; 4096x11008 8.6 / 14.6 /
+// 31.5 / 46.9 at M = 1 / 64 / 256 / 512 against 62.6 / 71.9 / 64.7 / 73.9.  It
+// loses on fuller grids (11008x4096 at M = 256: 40.5 against 39.6; 4096x4096 at
+// M = 768: 41.5 against 38.6), and needs K for at least two ranges.
 bool mx_split_wins(int64_t M, int64_t N, int64_t K) {
   return K >= 2 * kMxSplitMinChunks * kChunkK && (N + 127) / 128 * ((M + 127) / 128) <= 128;
 }

@@ -19,7 +19,8 @@
 // into registers and are expanded there into dense fp8 / fp4 fragments.
 // Weights and activations are requested two chunks before they are used.
 //
-// Split-K form (a caller-owned workspace): the grid also runs over ranges of
+// Split-K form (a caller-owned workspace; few tokens take gemm_mx_small.hip
+// instead, which splits K over the waves of a workgroup): the grid also runs over ranges of
 // the 128-K chunks; each workgroup writes the raw fp32 sums of its range to
 // the workspace, and a second kernel adds the ranges in order and scales by
 // s_a.  For tens to hundreds of tokens, where the one-pass grid alone leaves
@@ -315,7 +316,8 @@ hipError_t launch_mx_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int
   return launch_ms<4>(c, a, st);
 }
 
-// Split-K shape: token blocks of 32 tokens up to 32, 64 up to 64, else 128
+// Split-K shape, which also sizes the workspace of the calls that
+// mx_small_wins takes: token blocks of 32 tokens up to 32, 64 up to 64, else 128
 // (the K split, not the token block, fills the GPU), then K ranges of at
 // least kMxSplitMinChunks chunks until about kMxSplitTarget workgroups run
 // (two per CU).
@@ -345,6 +347,7 @@ size_t mx_split_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 hipError_t launch_mx_split(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                            const uint8_t* blob, int64_t N, int64_t K, void* Y, void* workspace,
                            hipStream_t st) {
+  if (mx_small_wins(M, N, K)) return launch_mx_small(c, Xq, s_a, M, blob, N, K, Y, st);
   const Layout L = make_layout(true, N, K);
   const MxSplitShape sh = mx_split_shape(M, N, K);
   MxArgs a{Xq, s_a, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles), L.scales_off};

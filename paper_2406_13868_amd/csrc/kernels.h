@@ -120,6 +120,12 @@ hipError_t launch_mx_split(const Cfg& c, const uint8_t* Xq, const float* s_a, in
                            const uint8_t* blob, int64_t N, int64_t K, void* Y, void* workspace,
                            hipStream_t st);
 
+// MX family, few tokens: K split over the waves of a workgroup, no workspace
+// (launch_mx_split takes it where mx_small_wins).
+bool mx_small_wins(int64_t M, int64_t N, int64_t K);
+hipError_t launch_mx_small(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M, const uint8_t* blob,
+                           int64_t N, int64_t K, void* Y, hipStream_t st);
+
 // Y[m, n] = s_a[m] * (part[0][m, n] + ... + part[S-1][m, n]), the ranges added
 // in order (part: [S][M][N] fp32, 16-byte aligned); fp32 or bf16 Y.
 hipError_t launch_split_reduce(const float* part, const float* s_a, void* Y, int64_t M, int64_t N, int S,

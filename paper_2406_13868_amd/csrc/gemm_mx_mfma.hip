@@ -319,8 +319,8 @@ hipError_t launch_mx_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int
 // Split-K shape, which also sizes the workspace of the calls that
 // mx_small_wins takes: token blocks of 32 tokens up to 32, 64 up to 64, else 128
 // (the K split, not the token block, fills the GPU), then K ranges of at
-// least kMxSplitMinChunks chunks until about kMxSplitTarget workgroups run
-// (two per CU).
+// least kMxSplitMinChunks chunks until up to kMxSplitTarget workgroups run
+// (two per CU: one round).
 constexpr int kMxSplitTarget = 512;
 
 struct MxSplitShape {
@@ -333,7 +333,10 @@ MxSplitShape mx_split_shape(int64_t M, int64_t N, int64_t K) {
   const int64_t kc = (K + kChunkK - 1) / kChunkK;
   s.MS = M <= 32 ? 1 : M <= 64 ? 2 : 4;
   const int64_t items = groups * std::max<int64_t>(1, (M + 32 * s.MS - 1) / (32 * s.MS));
-  int64_t S = (kMxSplitTarget + items - 1) / items;
+  // as many ranges as one round of kMxSplitTarget workgroups holds: a few more
+  // cost a second round (4096x11008 at M = 301, 96 items: 42.7 us with 6 ranges,
+  // 38.7 with 5; 2048x8192 at M = 301, 48 items: 26.0 with 11, 23.1 with 10)
+  int64_t S = items <= kMxSplitTarget / 2 ? kMxSplitTarget / items : (kMxSplitTarget + items - 1) / items;
   S = std::max<int64_t>(1, std::min<int64_t>(S, kc / kMxSplitMinChunks));
   s.kc_range = int((kc + S - 1) / S);
   s.S = int((kc + s.kc_range - 1) / s.kc_range);  // no empty range

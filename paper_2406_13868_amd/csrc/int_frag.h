@@ -38,9 +38,10 @@ __device__ __forceinline__ _Float16 block_scale(const uint32_t* sv, int kb, int 
     if constexpr (SF == kScaleE4M3) {
       return (_Float16)__builtin_amdgcn_cvt_f32_fp8(int(byte), 0);
     } else {
-      const uint32_t ex = byte >> 2, m = byte & 3u;
-      const float v = ex ? float(4u + m) * __uint_as_float((ex + 94u) << 23) : 0.f;  // code 0: scale 0
-      return (_Float16)v;
+      // (1 + m/4) * 2^(e - 31) as fp32 bits; e = 0 (scale 0) is below 2^-30 and
+      // rounds to 0.  No select: as one it became a branch on the lane, and the
+      // tiled kernel's products came out non-finite on some rows of W.
+      return (_Float16)__uint_as_float((byte << 21) + (96u << 23));
     }
   }
 }

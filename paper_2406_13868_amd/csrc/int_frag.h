@@ -39,8 +39,7 @@ __device__ __forceinline__ _Float16 block_scale(const uint32_t* sv, int kb, int 
       return (_Float16)__builtin_amdgcn_cvt_f32_fp8(int(byte), 0);
     } else {
       // (1 + m/4) * 2^(e - 31) as fp32 bits; e = 0 (scale 0) is below 2^-30 and
-      // rounds to 0.  No select: as one it became a branch on the lane, and the
-      // tiled kernel's products came out non-finite on some rows of W.
+      // rounds to 0 by itself, so no select is needed
       return (_Float16)__uint_as_float((byte << 21) + (96u << 23));
     }
   }

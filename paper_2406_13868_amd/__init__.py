@@ -16,7 +16,6 @@ from __future__ import annotations
 
 import ctypes as C
 import dataclasses
-import functools
 from typing import Dict, Optional
 
 import numpy as np
@@ -35,8 +34,15 @@ __all__ = ["Config", "pack", "pack_logical", "unpack_dense", "pack_size", "logic
 _FMT = {"int8": FMT_INT8, "int4": FMT_INT4, "e4m3": FMT_E4M3, "e2m1": FMT_E2M1}
 
 
+class _PerCall:
+    """What a call hands to the library, made once per Config (its fields never
+    change): the C structure by reference, and the pack sizes of the shapes it
+    was used with.  In slots, so that vars() of a Config is its fields."""
+    __slots__ = ("_ref", "_sizes")
+
+
 @dataclasses.dataclass(frozen=True)
-class Config:
+class Config(_PerCall):
     family: str = "int"      # "int" | "mx" | "dual"
     n_o: int = 1
     m_o: int = 8
@@ -138,19 +144,18 @@ class Config:
                                _lib.SCALE[self.sfmt_i],
                                {"f32": DTYPE_F32, "bf16": DTYPE_BF16}[self.y_dtype], self.qv_i)
 
-    # What a call hands to the library, made once per Config object (its fields
-    # never change): the C structure by reference, and the pack sizes of the
-    # shapes it was used with.
-    @functools.cached_property
-    def _ref(self):
-        return C.byref(self.c())
+    def __getattr__(self, name):  # the two of _PerCall, at their first use
+        if name == "_ref":
+            value = C.byref(self.c())
+        elif name == "_sizes":
+            value = {}
+        else:
+            raise AttributeError(f"{type(self).__name__!r} object has no attribute {name!r}")
+        object.__setattr__(self, name, value)
+        return value
 
-    @functools.cached_property
-    def _sizes(self) -> dict:
-        return {}
-
-    def __getstate__(self):  # the fields alone: a reference cannot be copied or pickled
-        return {f.name: getattr(self, f.name) for f in dataclasses.fields(self)}
+    def __getstate__(self):  # without the two: a reference cannot be copied or pickled
+        return dict(vars(self))
 
     def y_torch_dtype(self):
         torch = _torch()

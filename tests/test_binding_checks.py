@@ -2,6 +2,10 @@
 reaches the C ABI (which cannot see sizes): a wrong shape, dtype, length or
 byte count raises ValueError instead of becoming an out-of-bounds access on
 the GPU.  CPU only: the checks run before any device call."""
+import copy
+import dataclasses
+import pickle
+
 import numpy as np
 import pytest
 
@@ -87,3 +91,27 @@ def test_linear_checks_its_buffers():
     _raises(lambda: sdq.linear(X, blob, N, K, INT, xq=torch.empty((M + 1, K), dtype=torch.uint8)), "Xq must be")
     _raises(lambda: sdq.linear(X, blob, N, K, INT, scales=torch.empty((2 * M,))), "s_a must be")
     _raises(lambda: sdq.linear(X, blob[:8], N, K, INT), "packed holds")
+
+
+def test_a_used_config_still_holds_its_fields_alone():
+    """What a call keeps on a Config is not part of its state: the fields build
+    it again, and copies and pickles carry the fields (and a subclass's own
+    attributes) only."""
+    cfg = sdq.Config.int_family()
+    sdq.pack_size(cfg, N, K)
+    sdq.gemm_workspace_size(cfg, M, N, K)
+    fields = {f.name for f in dataclasses.fields(cfg)}
+    assert set(vars(cfg)) == fields and sdq.Config(**vars(cfg)) == cfg
+    tagged = Tagged()
+    object.__setattr__(tagged, "tag", 3)
+    sdq.pack_size(tagged, N, K)
+    for c in (cfg, tagged):
+        for other in (copy.copy(c), copy.deepcopy(c), pickle.loads(pickle.dumps(c)), dataclasses.replace(c)):
+            assert other == c and hash(other) == hash(c) and sdq.pack_size(other, N, K) == sdq.pack_size(c, N, K)
+    assert copy.copy(tagged).tag == pickle.loads(pickle.dumps(tagged)).tag == 3
+    with pytest.raises(AttributeError, match="'Config' object has no attribute 'nothing'"):
+        cfg.nothing
+
+
+class Tagged(sdq.Config):
+    pass

@@ -3,6 +3,7 @@ reaches the C ABI (which cannot see sizes): a wrong shape, dtype, length or
 byte count raises ValueError instead of becoming an out-of-bounds access on
 the GPU.  CPU only: the checks run before any device call."""
 import copy
+import ctypes
 import dataclasses
 import pickle
 
@@ -111,6 +112,17 @@ def test_a_used_config_still_holds_its_fields_alone():
     assert copy.copy(tagged).tag == pickle.loads(pickle.dumps(tagged)).tag == 3
     with pytest.raises(AttributeError, match="'Config' object has no attribute 'nothing'"):
         cfg.nothing
+
+
+@pytest.mark.parametrize("n", [float(N), np.int64(N), str(N)])
+def test_pack_size_refuses_what_is_no_int_whatever_was_asked_before(n):
+    cfg = sdq.Config.int_family()
+    for _ in range(2):  # before and after the shape is known
+        with pytest.raises((ctypes.ArgumentError, TypeError)):
+            sdq.pack_size(cfg, n, K)
+        with pytest.raises((ctypes.ArgumentError, TypeError)):
+            sdq.pack_size(cfg, N, type(n)(K))
+        assert sdq.pack_size(cfg, N, K) > 0
 
 
 class Tagged(sdq.Config):

@@ -175,7 +175,7 @@ _MAX_SIZES = 256  # shapes a Config remembers the pack size of
 
 def pack_size(cfg: Config, N: int, K: int) -> int:
     sizes = cfg._sizes
-    # (a float or a numpy integer equal to a size seen before is for the library to refuse)
+    # (a float equal to a size seen before is for the library to refuse)
     have = sizes.get((N, K)) if type(N) is type(K) is int else None
     if have is not None:
         return have

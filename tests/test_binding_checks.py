@@ -114,9 +114,10 @@ def test_a_used_config_still_holds_its_fields_alone():
         cfg.nothing
 
 
-@pytest.mark.parametrize("n", [float(N), np.int64(N), str(N)])
-def test_pack_size_refuses_what_is_no_int_whatever_was_asked_before(n):
+@pytest.mark.parametrize("n", [float(N), str(N)])
+def test_pack_size_refuses_what_is_no_integer_whatever_was_asked_before(n):
     cfg = sdq.Config.int_family()
+    assert sdq.pack_size(cfg, np.int64(N), K) == sdq.pack_size(sdq.Config.int_family(), N, K)
     for _ in range(2):  # before and after the shape is known
         with pytest.raises((ctypes.ArgumentError, TypeError)):
             sdq.pack_size(cfg, n, K)

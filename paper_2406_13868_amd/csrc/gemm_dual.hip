@@ -212,22 +212,46 @@ __global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(
     const uint32_t vo = ro * K + uint32_t(((otid & 7) ^ swz_o(ro)) * 16);
     const uint32_t vi = ri * (K / 2) + uint32_t(((itid & 3) ^ swz_i(ri)) * 16);
     const uint32_t pi = (uint32_t(itid) % (BM * 4)) * 16;
+    // A row's request for the four chunks from c & ~3 on is made early by d
+    // bytes where it would reach past the row's end, and its bytes move down:
+    // the slots of blocks past K then hold bytes of the same row.  The weights
+    // there are zero codes, which cancel any finite scale but not a NaN (0xFF),
+    // and a NaN of this row makes its outputs NaN anyway, whereas the bytes
+    // that follow in memory are the next row's.  (Masks in the loop instead:
+    // 4096x4096 at M = 256 in 15.6 us, not 14.2; a branch for the last chunks
+    // undid the loop's schedule, 11008x4096 at M = 4096 in 1300 us, not 239.)
+    const int eblocks = int(K / 32);
+    auto e_start = [&](int c) { return min((cb + (c & ~3)) * 4, eblocks - 16); };
+    auto e_row = [&](int c) { return re + uint32_t(c & 3) * (BM / 4); };
     auto load_e = [&](int c, v4i& e) __attribute__((always_inline)) {
-      const uint32_t row = re + uint32_t(c & 3) * (BM / 4) + eback;
-      e = ld16(ea, min(row * (K / 32) + uint32_t(cb + (c & ~3)) * 4, ebytes - 16), 0);
+      e = ld16(ea, (e_row(c) + eback) * (K / 32) + uint32_t(e_start(c)), 0);
     };
-    // A request that would reach past the end of the range was made early by
-    // d bytes; its bytes move down.  (Bytes past K are the next row's scales
-    // or unspecified: the weights there are zero codes.)
-    auto store_e = [&](int c, v4i e) __attribute__((always_inline)) {
-      const uint32_t r0 = re + uint32_t(c & 3) * (BM / 4);
-      const uint32_t off = (r0 + eback) * (K / 32) + uint32_t(cb + (c & ~3)) * 4;
-      const uint32_t d = off - min(off, ebytes - 16);
+    auto move_down = [](v4i& e, uint32_t d) __attribute__((always_inline)) {
       if (d & 8) { e[0] = e[2]; e[1] = e[3]; }
       if (d & 4) { e[0] = e[1]; e[1] = e[2]; e[2] = e[3]; }
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        ea_s[(((c & ~3) + j) & 15) * BM + r0] = __builtin_amdgcn_alignbyte(e[j < 3 ? j + 1 : 3], e[j], d & 3);
+      for (int j = 0; j < 4; ++j) e[j] = int(__builtin_amdgcn_alignbyte(e[j < 3 ? j + 1 : 3], e[j], d & 3));
+    };
+    auto store_e = [&](int c, v4i e) __attribute__((always_inline)) {
+      move_down(e, uint32_t((cb + (c & ~3)) * 4 - e_start(c)));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ea_s[(((c & ~3) + j) & 15) * BM + e_row(c)] = e[j];
+    };
+    // The same for the K group's first four chunks, whatever the row's length
+    // (a row of fewer than 16 blocks ends within them): early only where the
+    // buffer ends, and 2^0 for the blocks past K.
+    auto load_e0 = [&](int q, v4i& e) __attribute__((always_inline)) {
+      e = ld16(ea, min((e_row(q) + eback) * (K / 32) + uint32_t(cb) * 4, ebytes - 16), 0);
+    };
+    auto store_e0 = [&](int q, v4i e) __attribute__((always_inline)) {
+      const uint32_t off = (e_row(q) + eback) * (K / 32) + uint32_t(cb) * 4;
+      move_down(e, off - min(off, ebytes - 16));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int left = min(max(eblocks - 4 * (cb + j), 0), 4);  // blocks of the row in this dword
+        const uint32_t own = uint32_t((uint64_t(1) << (8 * left)) - 1);
+        ea_s[j * BM + e_row(q)] = (uint32_t(e[j]) & own) | (0x7F7F7F7Fu & ~own);
+      }
     };
     auto load_x1 = [&](int c, XRegs& x, int j) __attribute__((always_inline)) {
       const uint32_t cs = uint32_t(min(cb + c, last));
@@ -326,7 +350,7 @@ __global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(
       load_x(1, P1);
       if constexpr (ROLE == 0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) load_e(q, e0[q]);
+        for (int q = 0; q < 4; ++q) load_e0(q, e0[q]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -341,7 +365,7 @@ __global__ __launch_bounds__(KG * 2 * kDThreads, KG * 2) void dual_tiled_kernel(
       store_x(1, 1, P1);
       if constexpr (ROLE == 0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) store_e(q, e0[q]);
+        for (int q = 0; q < 4; ++q) store_e0(q, e0[q]);
       }
     }
     __syncthreads();

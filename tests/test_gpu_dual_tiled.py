@@ -57,3 +57,30 @@ def test_tiled_shapes_match_oracle(M, N, K, n_o, n_i, y_dtype):
     assert torch.equal(outs[0], outs[1])
     # nothing is written outside the output
     assert (buf[:skip] == 7.0).all() and (buf[skip + M * N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("n_o,n_i", [(1, 6), (2, 4)])
+@pytest.mark.parametrize("M,N,K", [(16, 256, 160),                       # split-K
+                                   (32, 8200, 160), (32, 8200, 384),     # 32 x 128; an odd number of chunks
+                                   (32, 8200, 1152), (32, 8200, 1408), (40, 8200, 1184),
+                                   (321, 4129, 160), (700, 4100, 160), (513, 8225, 160),
+                                   (321, 4129, 672), (700, 4100, 672), (513, 8225, 1184)])
+def test_a_nan_activation_scale_stays_in_its_token(M, N, K, n_o, n_i):
+    """The e8m0 NaN (0xFF, which a caller's own scales may hold) in the first
+    block of a token follows the last blocks of the token before it: with K no
+    whole number of chunks, or a second K group's chunk past K, that token's
+    scale reads reach it, and it must not reach the token's outputs."""
+    torch = torch_cuda()
+    cfg = sdq.Config("dual", n_o, 8, "int8", n_i, 8, "e2m1", "int8")
+    blob = torch.from_numpy(sdq.pack(synth.make_w(2, 0, N, K), cfg)).cuda()
+    Xo, s_a, Xi, Ea = sdq.quantize_act_dual(torch.from_numpy(synth.make_x(2, M, K)).cuda(), cfg)
+    say("dual nan scale", M, N, K, n_o)
+    clean = sdq.gemm_dual(Xo, s_a, Xi, Ea, blob, N, K, cfg)
+    nan = torch.zeros(M, dtype=torch.bool, device="cuda")
+    nan[1::5] = True
+    bad = Ea.clone()
+    bad[nan, 0] = 0xFF
+    Y = sdq.gemm_dual(Xo, s_a, Xi, bad, blob, N, K, cfg)
+    torch.cuda.synchronize()
+    assert torch.isnan(Y[nan]).all()
+    assert torch.equal(Y[~nan], clean[~nan]), f"{int((Y[~nan] != clean[~nan]).any(1).sum())} other tokens changed"

@@ -95,6 +95,38 @@ bool path_serves(const Cfg& c, int32_t path) {
   return true;  // SDQ_PATH_SPLITK: the INT and the MX family
 }
 
+// The kernel that a call takes on a path (AUTO resolved), for the log line and
+// the tests: from the launchers' own rules.
+void kernel_name(const Cfg& c, int32_t path, int64_t M, int64_t N, int64_t K, char* out, size_t n) {
+  if (c.dual) {
+    const char* const names[] = {"dual_decode",       "dual_splitk",       "dual_tiled 32x128",
+                                 "dual_tiled 64x128", "dual_tiled 64x256", "dual_tiled 128x256"};
+    std::snprintf(out, n, "%s", names[int(dual_form(M, N, K))]);
+  } else if (path == SDQ_PATH_DENSE) {
+    std::snprintf(out, n, "mx_dense (two passes)");
+  } else if (path == SDQ_PATH_SPLITK && c.mx && mx_small_wins(M, N, K)) {
+    std::snprintf(out, n, "mx_small");
+  } else if (path == SDQ_PATH_SPLITK) {
+    const KRanges r = c.mx ? mx_split_ranges(M, N, K) : int_split_ranges(M, N, K);
+    const char* const kernel = c.mx ? "mx_mfma" : int_split_tiled(M, N, K) ? "int_tiled" : "int_split";
+    std::snprintf(out, n, "%s %d (%d K range%s)", kernel, r.tokens, r.ranges, r.ranges == 1 ? "" : "s");
+  } else if (c.mx) {
+    std::snprintf(out, n, "mx_mfma %d", mx_mfma_tokens(M, N));
+  } else if (path == SDQ_PATH_DECODE) {
+    std::snprintf(out, n, "int_decode");
+  } else {
+    const char* const names[] = {"int_small", "int_splitk 32", "int_splitk 64", "int_tiled"};
+    std::snprintf(out, n, "%s", names[int(int_mfma_form(c, M, N))]);
+  }
+}
+
+void log_gemm(const Cfg& c, int32_t path, int64_t M, int64_t N, int64_t K, const char* note = "") {
+  if (!log_enabled()) return;
+  char name[64];
+  kernel_name(c, path, M, N, K, name, sizeof name);
+  std::fprintf(stderr, "[sdq] gemm M=%lld N=%lld K=%lld -> %s%s\n", (long long)M, (long long)N, (long long)K, name, note);
+}
+
 // The launchers report a failed launch through hipGetLastError, which also
 // returns an error that an earlier, unrelated HIP call on this thread left
 // pending (the runtime keeps one per thread until it is read).  Reading it
@@ -104,6 +136,18 @@ bool path_serves(const Cfg& c, int32_t path) {
 void drop_pending_error() { (void)hipGetLastError(); }
 
 }  // namespace
+
+// Not part of the C ABI (no declaration in sdq.h): kernel_name for the tests.
+extern "C" sdq_status sdq_kernel_name(const sdq_config* cfg, int64_t M, int64_t N, int64_t K, int32_t path, char* out,
+                                      size_t bytes) {
+  Cfg c;
+  const sdq_status s = check_config(cfg, N, K, &c);
+  if (s != SDQ_OK) return s;
+  if (!out) return SDQ_ERR_NULL;
+  if (path == SDQ_PATH_AUTO && !c.dual) path = auto_path_ws(c, M, N, K);
+  kernel_name(c, path, M, N, K, out, bytes);
+  return SDQ_OK;
+}
 
 extern "C" const char* sdq_status_string(sdq_status s) {
   switch (s) {
@@ -187,21 +231,10 @@ extern "C" sdq_status sdq_gemm_ex(const sdq_config* cfg, const void* Xq, const f
   const auto* blob = static_cast<const uint8_t*>(packed);
   const hipStream_t st = static_cast<hipStream_t>(stream);
   drop_pending_error();
-  hipError_t e;
-  const char* name;
-  if (c.mx) {
-    e = launch_mx_mfma(c, xq, s_a, M, blob, N, K, Y, st);
-    name = "mx_mfma";
-  } else if (path == SDQ_PATH_DECODE) {
-    e = launch_int_decode(c, xq, s_a, M, blob, N, K, Y, st);
-    name = "int_decode";
-  } else {
-    e = launch_int_mfma(c, xq, s_a, M, blob, N, K, Y, st);
-    name = "int_mfma";
-  }
-  if (log_enabled())
-    std::fprintf(stderr, "[sdq] gemm M=%lld N=%lld K=%lld -> %s\n", (long long)M, (long long)N,
-                 (long long)K, name);
+  const hipError_t e = c.mx                      ? launch_mx_mfma(c, xq, s_a, M, blob, N, K, Y, st)
+                       : path == SDQ_PATH_DECODE ? launch_int_decode(c, xq, s_a, M, blob, N, K, Y, st)
+                                                 : launch_int_mfma(c, xq, s_a, M, blob, N, K, Y, st);
+  log_gemm(c, path, M, N, K);
   return e == hipSuccess ? SDQ_OK : SDQ_ERR_HIP;
 }
 
@@ -246,9 +279,7 @@ extern "C" sdq_status sdq_gemm_ws(const sdq_config* cfg, const void* Xq, const f
   const hipError_t e = path == SDQ_PATH_DENSE ? launch_mx_dense(c, xq, s_a, M, blob, N, K, Y, workspace, st)
                        : c.mx                  ? launch_mx_split(c, xq, s_a, M, blob, N, K, Y, workspace, st)
                                                : launch_int_split(c, xq, s_a, M, blob, N, K, Y, workspace, st);
-  if (log_enabled())
-    std::fprintf(stderr, "[sdq] gemm M=%lld N=%lld K=%lld -> %s\n", (long long)M, (long long)N,
-                 (long long)K, path == SDQ_PATH_DENSE ? "mx_dense (two passes)" : c.mx ? "mx_split (K ranges)" : "int_split (K ranges)");
+  log_gemm(c, path, M, N, K);
   return e == hipSuccess ? SDQ_OK : SDQ_ERR_HIP;
 }
 
@@ -314,9 +345,7 @@ extern "C" sdq_status sdq_gemm_static(const sdq_config* cfg, const void* Xq, con
   drop_pending_error();
   const hipError_t e = path == SDQ_PATH_DENSE ? launch_mx_dense_static(c, xq, s_a, M, blob, N, K, Y, st)
                                               : split_static(c, xq, s_a, M, blob, N, K, Y, st);
-  if (log_enabled())
-    std::fprintf(stderr, "[sdq] gemm M=%lld N=%lld K=%lld -> %s, static scratch\n", (long long)M,
-                 (long long)N, (long long)K, path == SDQ_PATH_DENSE ? "mx_dense (two passes)" : "int_split");
+  log_gemm(c, path, M, N, K, ", static scratch");
   return e == hipSuccess ? SDQ_OK : SDQ_ERR_HIP;
 }
 
@@ -417,8 +446,6 @@ extern "C" sdq_status sdq_gemm_dual(const sdq_config* cfg, const void* Xq_o, con
                                         static_cast<const uint8_t*>(Xq_i), static_cast<const uint8_t*>(e_a_i),
                                         M, static_cast<const uint8_t*>(packed), N, K, Y,
                                         static_cast<hipStream_t>(stream));
-  if (log_enabled())
-    std::fprintf(stderr, "[sdq] gemm M=%lld N=%lld K=%lld -> dual_mfma\n", (long long)M, (long long)N,
-                 (long long)K);
+  log_gemm(c, SDQ_PATH_AUTO, M, N, K);
   return e == hipSuccess ? SDQ_OK : SDQ_ERR_HIP;
 }

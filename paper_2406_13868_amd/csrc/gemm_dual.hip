@@ -640,6 +640,22 @@ hipError_t launch_tiled(DualArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int NP>
+hipError_t launch_np(DualForm f, const DualArgs& a, hipStream_t st) {
+  switch (f) {
+    case DualForm::k32x128: return launch_tiled<1, 1, NP, 2>(a, st);
+    case DualForm::k64x128: return launch_tiled<2, 1, NP, 1>(a, st);
+    case DualForm::k64x256: return launch_tiled<2, 2, NP, 1>(a, st);
+    case DualForm::k128x256: return launch_tiled<4, 2, NP, 1>(a, st);
+    default: break;
+  }
+  const dim3 grid(unsigned(a.n_tiles), unsigned((a.M + 31) / 32));
+  hipLaunchKernelGGL((dual_splitk_kernel<4, NP>), grid, dim3(4 * 64), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 // The split-K form while its grid (one tile x 32 tokens per workgroup) stays
 // within one round, and up to 8 tokens: its waves gather activation rows
 // themselves, which costs by the row (4096x4096 at M = 16 / 64: 9.4 / 12.7 us
@@ -653,26 +669,19 @@ hipError_t launch_tiled(DualArgs a, hipStream_t st) {
 // 28.2, 35.6 / -, 60.7, 55.6, 46.0; 11008x4096 at M = 128 / 256 / 512: 24.9,
 // 17.7, 21.9, 29.6 / 37.2, 27.7, 24.4, 31.5 / 71.0, 42.5, 46.3, 36.7;
 // 4096x11008 at M = 256 / 768: 28.8, 35.8, 45.9, 63.6 / 81.2, 66.1, 52.8, 68.7.
-template <int NP>
-hipError_t launch_np(const DualArgs& a, hipStream_t st) {
-  const int64_t M = a.M;
-  // (the tiled form reads the activation scales 16 bytes at a time)
-  if (M <= 8 || int64_t(a.n_tiles) * ((M + 31) / 32) <= 256 || M * (a.K / 32) < 16) {
-    const dim3 grid(unsigned(a.n_tiles), unsigned((M + 31) / 32));
-    hipLaunchKernelGGL((dual_splitk_kernel<4, NP>), grid, dim3(4 * 64), 0, st, a);
-    return hipGetLastError();
-  }
-  const int64_t g4 = (a.n_tiles + 3) / 4, g8 = (a.n_tiles + 7) / 8;
+DualForm dual_form(int64_t M, int64_t N, int64_t K) {
+  if (dual_decode_fits(M, N, K)) return DualForm::kDecode;
+  const int64_t tiles = (N + kTileN - 1) / kTileN;
+  // (the tiled form's first scales are read 16 bytes at a time)
+  if (M <= 8 || tiles * ((M + 31) / 32) <= 256 || M * (K / 32) < 16) return DualForm::kSplitK;
+  const int64_t g4 = (tiles + 3) / 4, g8 = (tiles + 7) / 8;
   const auto rounds = [](int64_t wgs) { return (wgs + 255) / 256; };
   const int64_t c11 = 27 * rounds(g4 * ((M + 31) / 32)), c21 = 9 + 24 * rounds(g4 * ((M + 63) / 64));
   const int64_t c22 = 46 * rounds(g8 * ((M + 63) / 64)), c42 = 66 * rounds(g8 * ((M + 127) / 128));
-  if (c11 <= c21 && c11 <= c22 && c11 <= c42) return launch_tiled<1, 1, NP, 2>(a, st);
-  if (c21 <= c22 && c21 <= c42) return launch_tiled<2, 1, NP, 1>(a, st);
-  if (c22 <= c42) return launch_tiled<2, 2, NP, 1>(a, st);
-  return launch_tiled<4, 2, NP, 1>(a, st);
+  if (c11 <= c21 && c11 <= c22 && c11 <= c42) return DualForm::k32x128;
+  if (c21 <= c22 && c21 <= c42) return DualForm::k64x128;
+  return c22 <= c42 ? DualForm::k64x256 : DualForm::k128x256;
 }
-
-}  // namespace
 
 hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, const uint8_t* Xi,
                             const uint8_t* Ea, int64_t M, const uint8_t* blob, int64_t N, int64_t K,
@@ -682,8 +691,9 @@ hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, c
              L.out_off, L.scale_off, L.rows_off};
   a.y_bf16 = c.y_bf16;
   a.y_vec = out_vec(Y, N);
-  if (dual_decode_fits(M, N, K)) return launch_dual_decode(c, Xo, s_a, Xi, Ea, M, blob, N, K, Y, st);
-  return L.out_planes == 2 ? launch_np<2>(a, st) : launch_np<1>(a, st);
+  const DualForm f = dual_form(M, N, K);
+  if (f == DualForm::kDecode) return launch_dual_decode(c, Xo, s_a, Xi, Ea, M, blob, N, K, Y, st);
+  return L.out_planes == 2 ? launch_np<2>(f, a, st) : launch_np<1>(f, a, st);
 }
 
 }  // namespace sdq

@@ -549,6 +549,8 @@ TiledSplit tiled_split_shape(int64_t M, int64_t N, int64_t K) {
 
 }  // namespace
 
+KRanges int_tiled_split_ranges(int64_t M, int64_t N, int64_t K) { return {128, int(tiled_split_shape(M, N, K).S)}; }
+
 size_t int_tiled_split_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   return size_t(tiled_split_shape(M, N, K).S) * size_t(M) * size_t(N) * sizeof(float);
 }
@@ -570,20 +572,14 @@ hipError_t launch_int_tiled_split(const Cfg& c, const uint8_t* Xq, const float* 
   return launch_split_reduce(a.part, s_a, Y, M, N, int(t.S), c.y_bf16, st);
 }
 
-hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
-                           const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st) {
-  const Layout L = layout_for(c, N, K);
-  MfmaArgs a{Xq, s_a, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles),
-             L.scales_off, L.rows_off, L.irow_off};
-  a.y_bf16 = c.y_bf16;
-  a.qs = c.qv == 64 ? 2 : c.qv == 32 ? 1 : 0;
-  a.srow = (kChunkK / c.qv) * c.scale_bytes();
-  if (int_small_wins(c, M, N)) return launch_int_small(c, Xq, s_a, M, blob, N, K, Y, st);
-  if (M <= 32) return launch_ms<1>(c, a, st);
+IntForm int_mfma_form(const Cfg& c, int64_t M, int64_t N) {
+  if (int_small_wins(c, M, N)) return IntForm::kSmall;
+  if (M <= 32) return IntForm::kSplitK32;
+  const int64_t tiles = (N + kTileN - 1) / kTileN;
   // 33..64 tokens: one 64-token block expands every weight once; when that
   // leaves fewer workgroups than compute units, two 32-token blocks fill the
   // GPU instead (each weight is then expanded twice)
-  if (M <= 64) return L.n_tiles < kCUs ? launch_ms<1>(c, a, st) : launch_ms<2>(c, a, st);
+  if (M <= 64) return tiles < kCUs ? IntForm::kSplitK32 : IntForm::kSplitK64;
   // More tokens: the tiled kernel (four row tiles x 128 tokens per
   // workgroup, two workgroups per CU) or the split-K form over 64-token
   // blocks, whichever this cost model says is faster.  A tiled workgroup
@@ -596,12 +592,28 @@ hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, in
   // us).  The split-K form costs about 1/200 unit per workgroup's worth of
   // work, with no rounds (4096x4096 at M = 768 / 1024 / 1536: 83 / 109 /
   // 158 us; tiled 84 / 85 / 132).
-  const int64_t groups = (L.n_tiles + kWaves - 1) / kWaves;
+  const int64_t groups = (tiles + kWaves - 1) / kWaves;
   const int64_t w4 = groups * ((M + 127) / 128);
   const int64_t full = w4 / (2 * kCUs), rem = w4 % (2 * kCUs);
   const int64_t tail20 = rem == 0 ? 0 : rem > kCUs ? 34 : full > 0 ? 13 : 20;
   const int64_t tiled20 = 34 * full + tail20;            // tiled time x 20
-  if (w4 < 10 * tiled20) return launch_ms<2>(c, a, st);  // w4 / 200 units < tiled
+  return w4 < 10 * tiled20 ? IntForm::kSplitK64 : IntForm::kTiled;  // w4 / 200 units < tiled
+}
+
+hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
+                           const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st) {
+  const Layout L = layout_for(c, N, K);
+  MfmaArgs a{Xq, s_a, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles),
+             L.scales_off, L.rows_off, L.irow_off};
+  a.y_bf16 = c.y_bf16;
+  a.qs = c.qv == 64 ? 2 : c.qv == 32 ? 1 : 0;
+  a.srow = (kChunkK / c.qv) * c.scale_bytes();
+  switch (int_mfma_form(c, M, N)) {
+    case IntForm::kSmall: return launch_int_small(c, Xq, s_a, M, blob, N, K, Y, st);
+    case IntForm::kSplitK32: return launch_ms<1>(c, a, st);
+    case IntForm::kSplitK64: return launch_ms<2>(c, a, st);
+    case IntForm::kTiled: break;
+  }
   return launch_ms<4>(c, a, st);
 }
 

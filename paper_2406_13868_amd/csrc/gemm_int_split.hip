@@ -337,6 +337,12 @@ bool int_split_tiled(int64_t M, int64_t N, int64_t K) {
   return M > kSplitMaxM || K >= 8192 || N >= 16384 || (M <= 128 && N >= 8192);
 }
 
+KRanges int_split_ranges(int64_t M, int64_t N, int64_t K) {
+  if (int_split_tiled(M, N, K)) return int_tiled_split_ranges(M, N, K);
+  const SplitShape s = split_shape(M, N, K);
+  return {32 * s.MS, s.S};
+}
+
 size_t int_split_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   if (int_split_tiled(M, N, K)) return int_tiled_split_workspace_bytes(M, N, K);
   const SplitShape s = split_shape(M, N, K);

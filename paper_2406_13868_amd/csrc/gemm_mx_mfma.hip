@@ -298,22 +298,27 @@ hipError_t launch_ms(const Cfg& c, const MxArgs& a, hipStream_t st) {
 
 }  // namespace
 
+int mx_mfma_tokens(int64_t M, int64_t N) {
+  if (M <= 32) return 32;
+  if (M <= 64) return 64;
+  // More tokens: the largest token block that still gives a full round of
+  // workgroups wins (each block re-expands every weight it reads).  Measured
+  // at M = 128/256: 4096x4096 takes 26/27 us with 32-token blocks against
+  // 36/37 us with 128; 11008x4096 at M = 128 takes 31 us with 64 against 38.
+  const int64_t groups = ((N + kTileN - 1) / kTileN + kWaves - 1) / kWaves;
+  if (groups * ((M + 31) / 32) <= kCUs) return 32;
+  if (groups * ((M + 63) / 64) <= kCUs) return 64;
+  return 128;
+}
+
 hipError_t launch_mx_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                           const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st) {
   const Layout L = make_layout(true, N, K);
   MxArgs a{Xq, s_a, blob, Y, int(M), int(N), int(K), int(L.n_chunks), int(L.n_tiles), L.scales_off};
   a.y_bf16 = c.y_bf16;
   a.kc_range = int(L.n_chunks);
-  if (M <= 32) return launch_ms<1>(c, a, st);
-  if (M <= 64) return launch_ms<2>(c, a, st);
-  // More tokens: the largest token block that still gives a full round of
-  // workgroups wins (each block re-expands every weight it reads).  Measured
-  // at M = 128/256: 4096x4096 takes 26/27 us with 32-token blocks against
-  // 36/37 us with 128; 11008x4096 at M = 128 takes 31 us with 64 against 38.
-  const int64_t groups = (a.n_tiles + kWaves - 1) / kWaves;
-  if (groups * ((M + 31) / 32) <= kCUs) return launch_ms<1>(c, a, st);
-  if (groups * ((M + 63) / 64) <= kCUs) return launch_ms<2>(c, a, st);
-  return launch_ms<4>(c, a, st);
+  const int t = mx_mfma_tokens(M, N);
+  return t == 32 ? launch_ms<1>(c, a, st) : t == 64 ? launch_ms<2>(c, a, st) : launch_ms<4>(c, a, st);
 }
 
 // Split-K shape, which also sizes the workspace of the calls that
@@ -341,6 +346,11 @@ MxSplitShape mx_split_shape(int64_t M, int64_t N, int64_t K) {
   s.kc_range = int((kc + S - 1) / S);
   s.S = int((kc + s.kc_range - 1) / s.kc_range);  // no empty range
   return s;
+}
+
+KRanges mx_split_ranges(int64_t M, int64_t N, int64_t K) {
+  const MxSplitShape s = mx_split_shape(M, N, K);
+  return {32 * s.MS, s.S};
 }
 
 size_t mx_split_workspace_bytes(int64_t M, int64_t N, int64_t K) {

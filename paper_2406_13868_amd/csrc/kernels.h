@@ -62,7 +62,10 @@ bool dual_decode_fits(int64_t M, int64_t N, int64_t K);
 hipError_t launch_dual_decode(const Cfg& c, const uint8_t* Xo, const float* s_a, const uint8_t* Xi,
                               const uint8_t* Ea, int64_t M, const uint8_t* blob, int64_t N, int64_t K,
                               void* Y, hipStream_t st);
-// Dual family, matrix-core kernel (any M): fp4 x fp4 inliers and int8 x int8 outliers.
+// Dual family (any M): the decode kernel, or the matrix-core kernel (fp4 x fp4
+// inliers and int8 x int8 outliers) in the form dual_form names.
+enum class DualForm { kDecode, kSplitK, k32x128, k64x128, k64x256, k128x256 };
+DualForm dual_form(int64_t M, int64_t N, int64_t K);
 hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, const uint8_t* Xi,
                             const uint8_t* Ea, int64_t M, const uint8_t* blob, int64_t N, int64_t K,
                             void* Y, hipStream_t st);
@@ -81,7 +84,11 @@ hipError_t launch_int_decode_fused(const Cfg& c, const void* X, int x_dtype, int
 bool decode_fits(int64_t M, int64_t K);
 bool decode_fused_fits(int64_t M, int64_t K);
 
-// INT family, matrix-core kernel (any M).
+// INT family, matrix cores without a workspace (any M): int_small_kernel, the
+// form that splits K over a workgroup's waves (32 or 64 tokens), or the tiled
+// kernel, as int_mfma_form says.
+enum class IntForm { kSmall, kSplitK32, kSplitK64, kTiled };
+IntForm int_mfma_form(const Cfg& c, int64_t M, int64_t N);
 hipError_t launch_int_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                            const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st);
 
@@ -90,11 +97,17 @@ bool int_small_wins(const Cfg& c, int64_t M, int64_t N);
 hipError_t launch_int_small(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M, const uint8_t* blob,
                             int64_t N, int64_t K, void* Y, hipStream_t st);
 
+// A split of K over workgroups: tokens per block and number of K ranges.
+struct KRanges {
+  int tokens, ranges;
+};
+
 // INT family, matrix-core kernel with K split across workgroups (tens to a
 // few hundred tokens): partial sums of the K ranges in `workspace` (at least
 // int_split_workspace_bytes(M, N, K) bytes, 16-byte aligned), then a second
 // kernel adds them in range order and scales by s_a.
 constexpr int64_t kSplitMaxM = 256;
+KRanges int_split_ranges(int64_t M, int64_t N, int64_t K);
 size_t int_split_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_int_split(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                             const uint8_t* blob, int64_t N, int64_t K, void* Y, void* workspace,
@@ -103,18 +116,21 @@ hipError_t launch_int_split(const Cfg& c, const uint8_t* Xq, const float* s_a, i
 // blocks) over K ranges instead: partial sums in `workspace` (at least
 // int_tiled_split_workspace_bytes(M, N, K) bytes), the same second kernel.
 bool int_split_tiled(int64_t M, int64_t N, int64_t K);
+KRanges int_tiled_split_ranges(int64_t M, int64_t N, int64_t K);
 size_t int_tiled_split_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_int_tiled_split(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                                   const uint8_t* blob, int64_t N, int64_t K, void* Y, void* workspace,
                                   hipStream_t st);
 
-// MX family, scaled matrix-core kernel (any M).
+// MX family, scaled matrix-core kernel (any M), in blocks of mx_mfma_tokens.
+int mx_mfma_tokens(int64_t M, int64_t N);
 hipError_t launch_mx_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                           const uint8_t* blob, int64_t N, int64_t K, void* Y, hipStream_t st);
 // The same kernel with K split across workgroups: raw partial sums of the K
 // ranges in `workspace` (mx_split_workspace_bytes(M, N, K) bytes, 16-byte
 // aligned), then the split-K reduction below.
 constexpr int kMxSplitMinChunks = 4;  // 128-K chunks per K range, at least
+KRanges mx_split_ranges(int64_t M, int64_t N, int64_t K);
 size_t mx_split_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_mx_split(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M,
                            const uint8_t* blob, int64_t N, int64_t K, void* Y, void* workspace,

@@ -1,0 +1,57 @@
+"""The shapes of the GPU tests take the kernels that the tests name: every
+table of (shape, kernel) in them against the launchers' own rules.  CPU only,
+so that a changed rule is seen before a GPU run."""
+import pytest
+
+import paper_2406_13868_amd as sdq
+from tests import test_gpu_bf16_out as bf16_out
+from tests import test_gpu_dual as dual
+from tests import test_gpu_dual_tiled as dual_tiled
+from tests import test_gpu_gemm as gemm
+from tests import test_gpu_partial_chunk as partial
+from tests import test_zz_no_alloc as no_alloc
+from tests.gpu_util import kernel_of
+
+INT, MX, DUAL = sdq.Config.int_family(), sdq.Config.mx_family(), sdq.Config.dual_family()
+
+
+def _cases():
+    for M, N, K, kernel in dual.FORMS + dual_tiled.NAN_SHAPES:
+        yield DUAL, M, N, K, sdq.PATH_AUTO, kernel
+    for M, N, K, form in dual_tiled.SHAPES:
+        yield DUAL, M, N, K, sdq.PATH_AUTO, f"dual_tiled {form}"
+    for fam, M, N, K, kernel in gemm.KERNELS_ABOVE_64 + partial.KERNELS:
+        yield INT if fam == "int" else MX, M, N, K, sdq.PATH_MFMA, kernel
+    for M, N, K, fmt_o, kernel in gemm.INT_32_ROWS:
+        yield sdq.Config.int_family(fmt_o=fmt_o), M, N, K, sdq.PATH_MFMA, kernel
+    for M, N, K, kernel in gemm.MX_SPLITK:
+        yield MX, M, N, K, sdq.PATH_SPLITK, kernel
+    for fam, fmt_o, M, N, K, path, kernel in bf16_out.WIDE:
+        yield sdq.Config.int_family(fmt_o=fmt_o) if fam == "int" else MX, M, N, K, path, kernel
+    for fam, *shapes in no_alloc.STATIC_SPLITK:
+        for M, N, K, kernel in shapes:
+            yield INT if fam == "int" else MX, M, N, K, sdq.PATH_SPLITK, kernel
+
+
+@pytest.mark.parametrize("cfg,M,N,K,path,kernel", list(_cases()))
+def test_the_shape_takes_the_kernel(cfg, M, N, K, path, kernel):
+    assert kernel_of(cfg, M, N, K, path) == kernel
+
+
+def test_every_kernel_of_the_dispatch_is_named_by_a_test():
+    seen = {kernel.split(" (")[0] for *_, kernel in _cases()}
+    assert seen >= {"dual_splitk", "dual_tiled 32x128", "dual_tiled 64x128", "dual_tiled 64x256", "dual_tiled 128x256",
+                    "int_splitk 32", "int_splitk 64", "int_tiled", "int_split 32", "int_split 64", "int_tiled 128",
+                    "mx_small", "mx_mfma 32", "mx_mfma 64", "mx_mfma 128"}
+
+
+@pytest.mark.parametrize("cfg,M,N,K,kernel", [
+    (INT, 1, 4096, 4096, "int_decode"), (INT, 16, 4096, 4096, "int_small"), (INT, 64, 16384, 4096, "int_split 64 (4 K ranges)"),
+    (INT, 201, 4096, 11008, "int_tiled 128 (8 K ranges)"), (INT, 2048, 4096, 4096, "int_tiled"),
+    (MX, 1, 4096, 4096, "mx_small"), (MX, 301, 4096, 11008, "mx_mfma 128 (5 K ranges)"),
+    (MX, 16, 22016, 4096, "mx_mfma 32"), (MX, 16, 4096, 512, "mx_mfma 32"),
+    (MX, 2048, 11008, 4096, "mx_dense (two passes)"),
+    (DUAL, 1, 4096, 4096, "dual_decode"), (DUAL, 256, 4096, 4096, "dual_tiled 32x128"),
+    (DUAL, 4096, 11008, 4096, "dual_tiled 128x256")])
+def test_what_the_entry_points_choose_with_a_workspace(cfg, M, N, K, kernel):
+    assert kernel_of(cfg, M, N, K) == kernel

@@ -17,7 +17,7 @@ import pytest
 
 import synth
 from oracle import sdq as S
-from tests.gpu_util import mx_term_tol, say, torch_cuda
+from tests.gpu_util import kernel_of, mx_term_tol, say, torch_cuda
 
 import paper_2406_13868_amd as sdq
 
@@ -67,6 +67,29 @@ def test_gemm_bf16_is_rounded_fp32(cfg, M):
         Yb = sdq.gemm(Xq, s_a, blob, N, K, _bf16(cfg), path=path)
         torch.cuda.synchronize()
         _assert_rounded(Yb, Y32, f"M={M} path={path}")
+
+
+WIDE = [  # family, fmt_o, M, N, K, path, kernel
+    ("int", "e4m3", 400, 8192, 128, sdq.PATH_MFMA, "int_tiled"), ("int", "int8", 400, 8191, 128, sdq.PATH_MFMA, "int_tiled"),
+    ("int", "e4m3", 300, 2080, 1024, sdq.PATH_SPLITK, "int_tiled 128 (2 K ranges)"),
+    ("mx", "e4m3", 300, 2080, 1024, sdq.PATH_SPLITK, "mx_mfma 128 (2 K ranges)"),
+    ("mx", "e4m3", 50, 12400, 1184, sdq.PATH_SPLITK, "mx_mfma 64 (2 K ranges)"),
+]
+
+
+@pytest.mark.parametrize("fam,fmt_o,M,N,K,path,kernel", WIDE)
+def test_gemm_bf16_is_rounded_fp32_on_wide_layers(fam, fmt_o, M, N, K, path, kernel):
+    torch = torch_cuda()
+    cfg = _int(fmt_o) if fam == "int" else _mx(2)
+    assert kernel_of(cfg, M, N, K, path) == kernel
+    X = torch.from_numpy(synth.make_x(2, M, K)).cuda()
+    blob = torch.from_numpy(sdq.pack(synth.make_w(2, 0, N, K), cfg)).cuda()
+    Xq, s_a = sdq.quantize_act(X, cfg)
+    say("bf16 wide", kernel, M, N, K)
+    Y32 = sdq.gemm(Xq, s_a, blob, N, K, cfg, path=path)
+    Yb = sdq.gemm(Xq, s_a, blob, N, K, _bf16(cfg), path=path)
+    torch.cuda.synchronize()
+    _assert_rounded(Yb, Y32, kernel)
 
 
 @pytest.mark.parametrize("M", [1, 2, 16])

@@ -17,7 +17,7 @@ import pytest
 
 import synth
 from oracle import sdq as S
-from tests.gpu_util import REL_TOL, dual_term_tol, rel_errors, say, torch_cuda
+from tests.gpu_util import REL_TOL, dual_term_tol, kernel_of, rel_errors, say, torch_cuda
 
 import paper_2406_13868_amd as sdq
 
@@ -131,37 +131,27 @@ def test_gemm_dual_decode_grid_is_exact():
         assert np.array_equal(Y.astype(np.float64), Yref)
 
 
-def _tokens_per_block(M, N, K=128):
-    """The matrix form for this shape (above two tokens): "split" (one tile and
-    32 tokens per workgroup, K over its waves) while its grid stays within a
-    round (two on rows of 8192 and more), else the tiled kernel's token block
-    (32, 64 or 128): the smallest that keeps the GPU full, by workgroup count."""
-    split_grid = -(-N // 32) * -(-M // 32)
-    if M <= 32 or split_grid <= 256 or (K >= 8192 and split_grid <= 512):
-        return "split"
-    groups = -(-(-(-N // 32)) // 4)
-    if groups * -(-M // 32) <= 256:
-        return 32
-    if groups * -(-M // 64) <= 1024 and groups * -(-M // 128) < 512:
-        return 64
-    return 128
+FORMS = [  # M, N, K, kernel
+    (100, 4096, 512, "dual_tiled 32x128"), (96, 4096, 11008, "dual_tiled 32x128"),
+    (300, 32768, 128, "dual_tiled 64x128"), (2100, 4096, 128, "dual_tiled 64x128"),
+    (700, 4100, 512, "dual_tiled 64x256"),
+    (300, 16384, 256, "dual_tiled 128x256"), (1100, 4096, 128, "dual_tiled 128x256"),
+    (64, 4096, 4096, "dual_splitk"), (100, 256, 512, "dual_splitk"),
+]
 
 
-@pytest.mark.parametrize("M,N,K,block", [(100, 4096, 512, 32), (300, 16384, 256, 64),
-                                         (1100, 4096, 128, 64), (300, 32768, 128, 128),
-                                         (2100, 4096, 128, 128), (64, 4096, 4096, "split"),
-                                         (96, 4096, 11008, "split"), (100, 256, 512, "split")])
+@pytest.mark.parametrize("M,N,K,kernel", FORMS)
 @pytest.mark.parametrize("n_o,n_i", [(1, 6), (2, 4)])
-def test_gemm_dual_every_token_block(M, N, K, block, n_o, n_i):
-    """Shapes that take each token block of the tiled kernel, and the split-K
-    form beyond 32 tokens, with ragged M."""
-    assert _tokens_per_block(M, N, K) == block
+def test_gemm_dual_every_token_block(M, N, K, kernel, n_o, n_i):
+    """Shapes that take each form of the tiled kernel, and the split-K form
+    beyond 32 tokens, with ragged M."""
+    assert kernel_of(_cfgs(n_o, n_i)[0], M, N, K) == kernel
     cfg, cfg_o = _cfgs(n_o, n_i)
     X = synth.make_x(2, M, K)
     W = synth.make_w(2, 0, N, K)
-    say("gemm dual block", block, M, N, K)
+    say("gemm dual block", kernel, M, N, K)
     Y, _ = _run(X, W, cfg)
-    _check(Y, X, W, cfg_o, f"dual block={block} M={M} N={N} K={K}")
+    _check(Y, X, W, cfg_o, f"{kernel} M={M} N={N} K={K}")
 
 
 @pytest.mark.parametrize("M", [1, 2, 256])
@@ -176,13 +166,16 @@ def test_gemm_dual_llama_layer(M):
 
 
 @pytest.mark.parametrize("n_o,n_i", [(1, 6), (2, 4)])
-@pytest.mark.parametrize("M", [1, 2, 20, 64])
-def test_gemm_dual_integer_grid_is_exact(M, n_o, n_i):
+@pytest.mark.parametrize("M,N,kernel", [(1, 64, "dual_decode"), (2, 64, "dual_decode"), (20, 64, "dual_splitk"),
+                                        (64, 64, "dual_splitk"), (40, 8225, "dual_tiled 32x128"),
+                                        (321, 4129, "dual_tiled 64x128"), (700, 4100, "dual_tiled 64x256"),
+                                        (513, 8225, "dual_tiled 128x256")])
+def test_gemm_dual_integer_grid_is_exact(M, N, kernel, n_o, n_i):
     """Inputs on which every scale is 1 and every product and partial sum is
     representable: the output must equal the oracle exactly, on every form
     (decode, split-K, tiled) and with one or two outliers per group."""
     rng = np.random.default_rng(9)
-    N, K = 64, 512
+    K = 512
     # activations: amax 127 per token (s_a = 1 for A_o); every 32-K block's amax
     # 4 would give A_i codes of x itself, but a token has one amax: use blocks
     # whose values are e2m1 grid points times 2^E with E = floor(log2 amax) - 2
@@ -195,6 +188,7 @@ def test_gemm_dual_integer_grid_is_exact(M, n_o, n_i):
         W[:, 5::8] = rng.choice([-100.0, -9.0, 8.0, 77.0], (N, K // 8))  # the second outlier of a group
     W[:, 1::32] = 6.0                                # every inlier block amax 6: E = 0
     cfg, cfg_o = _cfgs(n_o, n_i)
+    assert kernel_of(cfg, M, N, K) == kernel
     Yref, _, (s_ao, Ea), L = S.reference(X, W, cfg_o)
     assert (s_ao == 1).all() and (L["scale_o"] == 1).all()
     assert (L["mask_o"].reshape(N, -1, 8).sum(-1) == n_o).all()
@@ -213,16 +207,18 @@ def test_dual_entry_points_refuse_other_families():
         sdq.quantize_act_dual(X, sdq.Config.int_family())
 
 
-@pytest.mark.parametrize("M", [1, 16, 130])
+@pytest.mark.parametrize("M,N,kernel", [(1, 512, "dual_decode"), (16, 512, "dual_splitk"), (130, 512, "dual_splitk"),
+                                        (40, 8224, "dual_tiled 32x128"), (700, 4100, "dual_tiled 64x256")])
 @pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
-def test_dual_hip_graph_replays_match_eager(M, y_dtype):
+def test_dual_hip_graph_replays_match_eager(M, N, kernel, y_dtype):
     """Both dual calls captured in a HIP graph (the decode, split-K and tiled
-    forms by M) give the eager result on every replay, with eager work in
+    forms) give the eager result on every replay, with eager work in
     between."""
     import dataclasses
     torch = torch_cuda()
     cfg = dataclasses.replace(_cfgs(1, 6)[0], y_dtype=y_dtype)
-    N, K = 512, 1024
+    K = 1024
+    assert kernel_of(cfg, M, N, K) == kernel
     X = torch.from_numpy(synth.make_x(2, M, K)).cuda().to(torch.bfloat16)
     blob = torch.from_numpy(sdq.pack(synth.make_w(2, 0, N, K), cfg)).cuda()
     Xo = torch.empty((M, K), dtype=torch.uint8, device="cuda")

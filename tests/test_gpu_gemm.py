@@ -10,7 +10,7 @@ import pytest
 
 import synth
 from oracle import sdq as S
-from tests.gpu_util import assert_close, assert_close_terms, say, torch_cuda
+from tests.gpu_util import assert_close, assert_close_terms, kernel_of, say, torch_cuda
 
 import paper_2406_13868_amd as sdq
 
@@ -236,37 +236,18 @@ def test_quantized_activations_feed_gemm_like_oracle():
     assert np.array_equal(Y.cpu().numpy(), Y2)
 
 
-def _kernel_for(fam, M, N):
-    """Which matrix-core kernel the launcher picks above 64 tokens (the cost
-    model the kernels' launchers state): INT "tiled" (128-token blocks, two
-    workgroups per CU) when its grid of w4 = ceil(N/128) x ceil(M/128)
-    workgroups, at 1.7 units of time per full round of 512 plus 1.7 for a
-    last round of more than 256, or for at most 256 1 unit alone and 0.65
-    after a full round, is faster than the split-K form at w4/200 units, else
-    "split-K"; MX token blocks of 32, 64 or 128 (the largest whose grid stays
-    within one round of 256 workgroups)."""
-    groups = -(-N // 128)
-    if fam == "int":
-        w4 = groups * -(-M // 128)
-        full, rem = divmod(w4, 512)
-        tail20 = 0 if rem == 0 else 34 if rem > 256 else 13 if full else 20
-        return "split-K" if w4 < 10 * (34 * full + tail20) else "tiled"
-    if groups * -(-M // 32) <= 256:
-        return "block32"
-    if groups * -(-M // 64) <= 256:
-        return "block64"
-    return "block128"
+KERNELS_ABOVE_64 = [  # family, M, N, K, kernel
+    ("int", 100, 70, 256, "int_splitk 64"), ("int", 384, 8192, 256, "int_splitk 64"), ("int", 400, 8192, 128, "int_tiled"),
+    ("int", 700, 2048, 128, "int_splitk 64"), ("int", 1000, 8192, 128, "int_tiled"), ("int", 770, 16384, 256, "int_tiled"),
+    ("int", 1300, 8192, 128, "int_tiled"),
+    ("mx", 100, 70, 256, "mx_mfma 32"), ("mx", 200, 8192, 256, "mx_mfma 64"), ("mx", 300, 8192, 128, "mx_mfma 128"),
+]
 
 
-@pytest.mark.parametrize("fam,M,N,K,kernel", [("int", 100, 70, 256, "split-K"), ("int", 384, 8192, 256, "split-K"),
-                                              ("int", 400, 8192, 128, "tiled"), ("int", 700, 2048, 128, "split-K"),
-                                              ("int", 1000, 8192, 128, "tiled"), ("int", 770, 16384, 256, "tiled"),
-                                              ("int", 1300, 8192, 128, "tiled"),
-                                              ("mx", 100, 70, 256, "block32"), ("mx", 200, 8192, 256, "block64"),
-                                              ("mx", 300, 8192, 128, "block128")])
+@pytest.mark.parametrize("fam,M,N,K,kernel", KERNELS_ABOVE_64)
 def test_every_matrix_kernel_above_64_tokens(fam, M, N, K, kernel):
     """Shapes that take each matrix-core kernel and token block past 64 tokens, ragged M."""
-    assert _kernel_for(fam, M, N) == kernel
+    assert kernel_of(_cfgs(fam, 1, 8, "e4m3", 2)[0], M, N, K, sdq.PATH_MFMA) == kernel
     cfg, cfg_o = _cfgs(fam, 1, 8, "e4m3", 3 if fam == "int" else 2)
     X = synth.make_x(1, M, K)
     W = synth.make_w(1, 0, N, K)
@@ -274,6 +255,33 @@ def test_every_matrix_kernel_above_64_tokens(fam, M, N, K, kernel):
     Y, _, _, _ = run_gpu(X, W, cfg, path=sdq.PATH_MFMA)
     Yref, _, _, _ = S.reference(X, W, cfg_o)
     check(Y, Yref, X, W, cfg_o, f"{fam} {kernel} M={M} N={N} K={K}")
+
+
+INT_32_ROWS = [  # M, N, K, fmt_o, kernel: few tokens on layers too wide for int_small_kernel
+    (33, 4100, 416, "e4m3", "int_splitk 32"), (63, 4129, 2080, "int8", "int_splitk 32"),
+    (33, 4100, 2176, "e4m3", "int_splitk 32"), (20, 4130, 288, "int8", "int_splitk 32"),
+    (17, 12300, 160, "e4m3", "int_splitk 32"), (50, 8200, 288, "e4m3", "int_splitk 64"),
+    (33, 8200, 128, "int8", "int_splitk 64"),
+]
+
+
+@pytest.mark.parametrize("sfmt_i,qv,n_i", [("", 0, 3), ("", 32, 2), ("e4m3", 0, 1), ("ue6m2", 32, 3)])
+@pytest.mark.parametrize("M,N,K,fmt_o,kernel", INT_32_ROWS)
+def test_few_tokens_in_32_row_tiles(M, N, K, fmt_o, kernel, sfmt_i, qv, n_i):
+    """The matrix-core form that splits K over a workgroup's waves (four, or
+    eight on rows of 2048 and more), at 17 to 63 tokens on layers that
+    int_small_kernel leaves to it: ragged tokens and rows, a partial chunk,
+    every scale format, both outlier types."""
+    import dataclasses
+    cfg, cfg_o = _cfgs("int", 1, 8, fmt_o, n_i)
+    cfg = dataclasses.replace(cfg, sfmt_i=sfmt_i, qv_i=qv)
+    cfg_o = dataclasses.replace(cfg_o, sfmt_i=sfmt_i, qv=qv)
+    assert kernel_of(cfg, M, N, K, sdq.PATH_MFMA) == kernel
+    X = synth.make_x(4, M, K)
+    W = synth.make_w(4, 5, N, K)
+    say("int 32-row tiles", M, N, K, fmt_o, sfmt_i, qv)
+    Y, _, _, _ = run_gpu(X, W, cfg, sdq.PATH_MFMA)
+    check(Y, S.reference(X, W, cfg_o)[0], X, W, cfg_o, f"{kernel} M={M} N={N} K={K}")
 
 
 @pytest.mark.parametrize("c", [INT_CFGS[0], INT_CFGS[1], MX_CFGS[0]], ids=_ids)
@@ -377,7 +385,7 @@ def test_hip_graph_replays_match_eager(c):
         torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("which", ["mx-dense", "int-splitk", "mx-splitk"])
+@pytest.mark.parametrize("which", ["mx-dense", "int-splitk", "mx-splitk", "mx-ranges"])
 def test_hip_graph_replays_match_eager_two_pass(which):
     """The workspace paths (two-pass MX, INT and MX split-K; workspace
     allocated before capture) replay like eager, whatever the workspace held."""
@@ -388,6 +396,11 @@ def test_hip_graph_replays_match_eager_two_pass(which):
     elif which == "mx-splitk":
         cfg, _ = _cfgs(*MX_CFGS[1])
         N, K, M, path = 1000, 2304, 200, sdq.PATH_SPLITK
+        assert kernel_of(cfg, M, N, K, path) == "mx_small"
+    elif which == "mx-ranges":
+        cfg, _ = _cfgs(*MX_CFGS[1])
+        N, K, M, path = 2080, 2304, 300, sdq.PATH_SPLITK
+        assert kernel_of(cfg, M, N, K, path) == "mx_mfma 128 (4 K ranges)"
     else:
         cfg, _ = _cfgs(*INT_CFGS[1])
         N, K, M, path = 1000, 2304, 100, sdq.PATH_SPLITK
@@ -438,13 +451,24 @@ def test_split_k_ragged_shapes(c, M, N, K):
     check(Y, Yref, X, W, cfg_o, f"{_ids(c)} M={M} N={N} K={K} split-K")
 
 
+MX_SPLITK = [  # M, N, K, kernel
+    (9, 4128, 512, "mx_small"), (33, 97, 4096, "mx_small"), (64, 1000, 16384, "mx_small"), (100, 544, 1152, "mx_small"),
+    (129, 64, 8192, "mx_small"), (511, 33, 1024, "mx_small"),
+    (50, 12400, 1184, "mx_mfma 64 (2 K ranges)"), (64, 16384, 1024, "mx_mfma 64 (2 K ranges)"),
+    (33, 1000, 16384, "mx_mfma 64 (32 K ranges)"),
+    (256, 4096, 4096, "mx_mfma 128 (8 K ranges)"), (300, 2080, 640, "mx_mfma 128 (1 K range)"),
+    (300, 1000, 9024, "mx_mfma 128 (15 K ranges)"), (300, 2080, 1184, "mx_mfma 128 (2 K ranges)"),
+]
+
+
 @pytest.mark.parametrize("c", [MX_CFGS[0], MX_CFGS[1], MX_CFGS[4]], ids=_ids)
-@pytest.mark.parametrize("M,N,K", [(9, 4128, 512), (33, 97, 4096), (64, 1000, 16384), (100, 544, 1152),
-                                   (129, 64, 8192), (256, 4096, 4096), (300, 2080, 640), (511, 33, 1024)])
-def test_mx_split_k_ragged_shapes(c, M, N, K):
-    """The MX family's split-K path on shapes that give 1 to 32 K ranges,
-    every token block and ragged tiles, against the oracle."""
+@pytest.mark.parametrize("M,N,K,kernel", MX_SPLITK)
+def test_mx_split_k_ragged_shapes(c, M, N, K, kernel):
+    """The MX family's split-K path on shapes that take the few-token kernel,
+    or 1 to 32 K ranges with either token block, and ragged tiles, against the
+    oracle."""
     cfg, cfg_o = _cfgs(*c)
+    assert kernel_of(cfg, M, N, K, sdq.PATH_SPLITK) == kernel
     X = synth.make_x(4, M, K)
     W = synth.make_w(4, 4, N, K)
     Yref, _, _, _ = S.reference(X, W, cfg_o)
@@ -476,8 +500,9 @@ def _split_case(kind, N, K, rng):
 
 @pytest.mark.parametrize("kind", ["product", "zero_inliers", "huge_outliers"])
 @pytest.mark.parametrize("n_i", [2, 3])
-@pytest.mark.parametrize("M,N,K", [(64, 96, 512), (256, 64, 1024), (520, 96, 384)])
-@pytest.mark.parametrize("path", [sdq.PATH_MFMA, sdq.PATH_DENSE, sdq.PATH_SPLITK])
+@pytest.mark.parametrize("M,N,K,path", [(M, N, K, path) for M, N, K in ((64, 96, 512), (256, 64, 1024), (520, 96, 384))
+                                        for path in (sdq.PATH_MFMA, sdq.PATH_DENSE, sdq.PATH_SPLITK)]
+                         + [(300, 2080, 1024, sdq.PATH_SPLITK)])  # (K ranges; the others take the few-token kernel)
 def test_mx_unmergeable_blocks(kind, n_i, M, N, K, path):
     """The matrix kernel's correction path for blocks that stay split."""
     rng = np.random.default_rng(7)

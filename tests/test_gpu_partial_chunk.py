@@ -8,8 +8,8 @@ import pytest
 
 import synth
 from oracle import sdq as S
-from tests.gpu_util import assert_close, say, torch_cuda
-from tests.test_gpu_gemm import _cfgs, _ids, _kernel_for, check, run_gpu, INT_CFGS, MX_CFGS
+from tests.gpu_util import assert_close, kernel_of, say, torch_cuda
+from tests.test_gpu_gemm import _cfgs, _ids, check, run_gpu, INT_CFGS, MX_CFGS
 
 import paper_2406_13868_amd as sdq
 
@@ -32,12 +32,15 @@ def test_int_paths(c, M, N, K):
         check(Y, Yref, X, W, cfg_o, f"{_ids(c)} M={M} N={N} K={K} path={path}")
 
 
-@pytest.mark.parametrize("fam,M,N,K,kernel", [("int", 400, 8192, 160, "tiled"), ("int", 700, 2048, 288, "split-K"),
-                                              ("int", 1000, 8192, 160, "tiled"),
-                                              ("mx", 100, 70, 160, "block32"), ("mx", 200, 8192, 288, "block64"),
-                                              ("mx", 300, 8192, 160, "block128")])
+KERNELS = [  # family, M, N, K, kernel
+    ("int", 400, 8192, 160, "int_tiled"), ("int", 700, 2048, 288, "int_splitk 64"), ("int", 1000, 8192, 160, "int_tiled"),
+    ("mx", 100, 70, 160, "mx_mfma 32"), ("mx", 200, 8192, 288, "mx_mfma 64"), ("mx", 300, 8192, 160, "mx_mfma 128"),
+]
+
+
+@pytest.mark.parametrize("fam,M,N,K,kernel", KERNELS)
 def test_every_matrix_kernel(fam, M, N, K, kernel):
-    assert _kernel_for(fam, M, N) == kernel
+    assert kernel_of(_cfgs(fam, 1, 8, "e4m3", 2)[0], M, N, K, sdq.PATH_MFMA) == kernel
     cfg, cfg_o = _cfgs(fam, 1, 8, "e4m3", 3 if fam == "int" else 2)
     X = synth.make_x(6, M, K)
     W = synth.make_w(6, 1, N, K)

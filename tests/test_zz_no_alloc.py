@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import synth
-from tests.gpu_util import say, torch_cuda
+from tests.gpu_util import kernel_of, say, torch_cuda
 
 import paper_2406_13868_amd as sdq
 from paper_2406_13868_amd import _lib
@@ -67,14 +67,23 @@ def test_static_entry_refuses_a_workspace_beyond_the_array():
     assert e.value.status == -8
 
 
-@pytest.mark.parametrize("fam", ["int", "mx"])
-def test_static_entry_equals_workspace_entry_split_k(fam):
+STATIC_SPLITK = [  # family, two shapes (M, N, K, kernel), the second smaller
+    ("int", (64, 4128, 16384, "int_split 64 (16 K ranges)"), (20, 1000, 2048, "int_split 32 (4 K ranges)")),
+    ("mx", (64, 4128, 16384, "mx_small"), (20, 1000, 2048, "mx_small")),
+    ("mx", (256, 4096, 4096, "mx_mfma 128 (8 K ranges)"), (300, 2080, 1152, "mx_mfma 128 (2 K ranges)")),
+]
+
+
+@pytest.mark.parametrize("fam,first,second", STATIC_SPLITK)
+def test_static_entry_equals_workspace_entry_split_k(fam, first, second):
     """The split-K paths of the INT and MX families (partial sums of K ranges
-    in the scratch array): two calls in a row, the second smaller, each bit
-    for bit equal to sdq_gemm_ws with a caller-owned workspace."""
+    in the scratch array, or the MX kernel for few tokens, which writes none):
+    two calls in a row, the second smaller, each bit for bit equal to
+    sdq_gemm_ws with a caller-owned workspace."""
     torch = torch_cuda()
     cfg = sdq.Config.int_family(1, 8, "int8", 3) if fam == "int" else CFG
-    for (M, N, K, seed) in ((64, 4128, 16384, 1), (20, 1000, 2048, 2)):
+    for seed, (M, N, K, kernel) in enumerate((first, second), 1):
+        assert kernel_of(cfg, M, N, K, sdq.PATH_SPLITK) == kernel
         assert 0 < sdq.gemm_workspace_size(cfg, M, N, K, sdq.PATH_SPLITK) <= _lib.STATIC_SCRATCH_BYTES
         W = synth.make_w(4, 10 + seed, N, K)
         blob = torch.from_numpy(sdq.pack(W, cfg)).cuda()

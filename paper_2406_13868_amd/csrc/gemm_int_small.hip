@@ -160,7 +160,7 @@ __global__ __launch_bounds__(NW * 64) void int_small_kernel(SmallArgs a) {
           }
         }
       } else {
-        const h8 bo = outlier_f16<false>(w);
+        const h8 bo = outlier_f16(w);
 #pragma unroll
         for (int t = 0; t < MT; ++t) acco[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bo, av[t], acco[t], 0, 0, 0);
       }

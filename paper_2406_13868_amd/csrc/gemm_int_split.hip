@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kSplitThreads) void int_split_kernel(SplitArgs a) {
           }
         }
       } else {
-        const h8 bo = outlier_f16<false>(w);
+        const h8 bo = outlier_f16(w);
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms) acco[ms] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[ms], bo, acco[ms], 0, 0, 0);
       }

@@ -322,10 +322,11 @@ hipError_t launch_mx_mfma(const Cfg& c, const uint8_t* Xq, const float* s_a, int
 }
 
 // Split-K shape, which also sizes the workspace of the calls that
-// mx_small_wins takes: token blocks of 32 tokens up to 32, 64 up to 64, else 128
-// (the K split, not the token block, fills the GPU), then K ranges of at
-// least kMxSplitMinChunks chunks until up to kMxSplitTarget workgroups run
-// (two per CU: one round).
+// mx_small_wins takes (they must pass it and do not use it): token blocks of 32
+// tokens up to 32 (for the size alone: mx_small_wins takes all of those), 64 up
+// to 64, else 128 (the K split, not the token block, fills the GPU), then K
+// ranges of at least kMxSplitMinChunks chunks until up to kMxSplitTarget
+// workgroups run (two per CU: one round).
 constexpr int kMxSplitTarget = 512;
 
 struct MxSplitShape {
@@ -340,7 +341,9 @@ MxSplitShape mx_split_shape(int64_t M, int64_t N, int64_t K) {
   const int64_t items = groups * std::max<int64_t>(1, (M + 32 * s.MS - 1) / (32 * s.MS));
   // as many ranges as one round of kMxSplitTarget workgroups holds: a few more
   // cost a second round (4096x11008 at M = 301, 96 items: 42.7 us with 6 ranges,
-  // 38.7 with 5; 2048x8192 at M = 301, 48 items: 26.0 with 11, 23.1 with 10)
+  // 38.7 with 5; 2048x8192 at M = 301, 48 items: 26.0 with 11, 23.1 with 10).
+  // Above half a round of items, which only an explicit SDQ_PATH_SPLITK
+  // reaches, two ranges (up to two rounds) below a full one and then one.
   int64_t S = items <= kMxSplitTarget / 2 ? kMxSplitTarget / items : (kMxSplitTarget + items - 1) / items;
   S = std::max<int64_t>(1, std::min<int64_t>(S, kc / kMxSplitMinChunks));
   s.kc_range = int((kc + S - 1) / S);
@@ -367,8 +370,8 @@ hipError_t launch_mx_split(const Cfg& c, const uint8_t* Xq, const float* s_a, in
   a.k_ranges = sh.S;
   a.kc_range = sh.kc_range;
   a.part = static_cast<float*>(workspace);
-  const hipError_t e = sh.MS == 1 ? launch_ms<1>(c, a, st) : sh.MS == 2 ? launch_ms<2>(c, a, st)
-                                                                        : launch_ms<4>(c, a, st);
+  // (mx_small_wins takes every M <= 32, so no 32-token blocks here)
+  const hipError_t e = sh.MS <= 2 ? launch_ms<2>(c, a, st) : launch_ms<4>(c, a, st);
   if (e != hipSuccess) return e;
   return launch_split_reduce(a.part, s_a, Y, M, N, sh.S, c.y_bf16, st);
 }

@@ -45,15 +45,6 @@ __device__ __forceinline__ _Float16 block_scale(const uint32_t* sv, int kb, int 
   }
 }
 
-// A row's inlier scales of one chunk (srow = 16, 8, 4 or 2 bytes, naturally
-// aligned), into the low end of four dwords.
-__device__ __forceinline__ uint4 load_row_scales_chunk(const uint8_t* p, int srow) {
-  if (srow == 16) return *reinterpret_cast<const uint4*>(p);
-  if (srow == 8) { const uint2 v = *reinterpret_cast<const uint2*>(p); return make_uint4(v.x, v.y, 0, 0); }
-  if (srow == 4) return make_uint4(*reinterpret_cast<const uint32_t*>(p), 0, 0, 0);
-  return make_uint4(*reinterpret_cast<const uint16_t*>(p), 0, 0, 0);
-}
-
 // Four int8 -> four f16 (two dwords), exact: f16(1024 + (b ^ 0x80)) - 1152 = b.
 __device__ __forceinline__ void i8x4_to_f16x4(uint32_t x, uint32_t& lo, uint32_t& hi) {
   const uint32_t xb = x ^ 0x80808080u;
@@ -112,15 +103,12 @@ __device__ __forceinline__ void scaled_hi_lo(h8 q, _Float16 s, h8& hi, h8& lo) {
   lo = __builtin_elementwise_fma(q, sv, -hi);
 }
 
-// Dense fp16 outlier fragment of one group word (one non-zero at most).  The
+// Dense fp16 fragment of one group word's e4m3 outlier (one non-zero at most).  The
 // position bits gather as in outlier_i8, here into 16 * position (bits 20-23
 // of the product are zero too); one 64-bit shift places the fp16 value in
 // its half of the fragment and the position's top bit picks the half.
-template <bool OUT_INT8>
 __device__ __forceinline__ h8 outlier_f16(uint32_t w) {
-  float f;
-  if constexpr (OUT_INT8) f = (float)(int(w) >> 24);
-  else f = __builtin_amdgcn_cvt_f32_fp8(int(w), 3);
+  const float f = __builtin_amdgcn_cvt_f32_fp8(int(w), 3);
   const uint32_t hb = uint32_t(__builtin_bit_cast(unsigned short, (_Float16)f));
   const uint32_t p16 = __builtin_amdgcn_ubfe(__umul24(w & 0x00080808u, kOutPosMagic), 20, 7);
   const uint64_t v = uint64_t(hb) << (p16 & 63u);

@@ -314,28 +314,37 @@ sdq_status sdq_gemm_path_ws(const sdq_config* cfg, int64_t M, int64_t N, int64_t
  * SDQ_PATH_SPLITK splits K into ranges of 128-K chunks handled by different
  * workgroups; the partial sums of the ranges go to the workspace and a
  * second kernel adds them in range order and scales by s_a.  In the INT
- * family (9 to 256 tokens) each workgroup converts its activations to the
- * matrix instruction's f16 once for four row tiles; in the MX family (from
- * one token up to a few hundred) it is the one-pass scaled-MFMA kernel over
- * a range of K, so that a small grid still fills the GPU.  SDQ_PATH_DENSE, the two-pass matrix-core path of the MX
+ * family (9 to 256 tokens, and more on layers that leave the GPU part empty)
+ * each workgroup converts its activations to the matrix instruction's f16 once
+ * for four row tiles; in the MX family (up to a few hundred tokens) it is the
+ * one-pass scaled-MFMA kernel over a range of K, so that a small grid still
+ * fills the GPU.  With few tokens (always up to 32, more on small layers) the
+ * MX family instead runs one kernel that splits K over the waves of a
+ * workgroup and adds their sums there: the workspace is still required and
+ * checked, and not written.
+ * SDQ_PATH_DENSE, the two-pass matrix-core path of the MX
  * family with outliers, first expands every packed weight once into the dense
  * fp8 B operand of the matrix instruction (both branches of a 32-K block
  * merged into one e4m3 value per position under the outlier's e8m0 scale,
  * wherever the inliers fit it) and then multiplies those operands, so that
  * the expansion runs once per weight instead of once per weight and block of
  * 128 tokens (at 512 tokens and more the two passes take less time).
- *   path   SDQ_PATH_AUTO (what sdq_gemm_ws takes: SDQ_PATH_DENSE for the MX
- *          family with outliers when M >= 512 and ceil(N/256) * ceil(M/128)
- *          >= 160; SDQ_PATH_SPLITK for the MX family when K >= 1024 and
- *          ceil(N/128) * ceil(M/128) <= 128, and for the INT family up to
- *          256 tokens where sdq_gemm would take the matrix cores and K >=
- *          8192, or M >= 64 and N >= 8192, or M = 256; else what sdq_gemm
- *          takes), or SDQ_PATH_DECODE / SDQ_PATH_MFMA / SDQ_PATH_DENSE /
- *          SDQ_PATH_SPLITK
+ *   path   SDQ_PATH_AUTO (what sdq_gemm_ws takes), or SDQ_PATH_DECODE /
+ *          SDQ_PATH_MFMA / SDQ_PATH_DENSE / SDQ_PATH_SPLITK.  AUTO is
+ *          SDQ_PATH_DENSE for the MX family with outliers when M >= 512 and
+ *          ceil(N/256) * ceil(M/128) >= 160; SDQ_PATH_SPLITK for the MX family
+ *          when K >= 1024 and ceil(N/128) * ceil(M/128) <= 128; SDQ_PATH_SPLITK
+ *          for the INT family, where sdq_gemm would take the matrix cores,
+ *          when K >= 8192, or M >= 64 and N >= 8192, or M = 256 (up to 256
+ *          tokens), or K >= 1024 and ceil(N/128) * ceil(M/128) < 384 (above),
+ *          except for calls with K < 16384 that its kernel for few tokens
+ *          takes without a workspace (up to 16 tokens; up to 64 while
+ *          ceil(N/32) * ceil(M/32) <= 128; up to 32 with e4m3 outliers and N
+ *          <= 12288); else what sdq_gemm takes
  *   bytes  32 * ceil(N / 32) * K for SDQ_PATH_DENSE; 4 * S * M * N for
  *          SDQ_PATH_SPLITK, with S (the number of K ranges, at most
  *          ceil(K / 128) / 4) chosen from M, N and K so that about 2048
- *          waves (INT) or 512 workgroups (MX) run; 0 for the other paths
+ *          waves (INT) or up to 512 workgroups (MX) run; 0 for the other paths
  * Returns SDQ_ERR_UNSUPPORTED for SDQ_PATH_DENSE outside the MX family with
  * outliers and for SDQ_PATH_SPLITK in the dual family. */
 sdq_status sdq_gemm_workspace_size(const sdq_config* cfg, int64_t M, int64_t N, int64_t K,

@@ -241,13 +241,16 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 
 }  // namespace
 
-// Up to 32 tokens always, up to 64 on up to 12288 rows (us per call, this
-// kernel against the K ranges with their second pass: 4096x4096 at M = 1 / 16 /
+// On SDQ_PATH_SPLITK alone, against the K ranges with their second pass; AUTO
+// takes that path up to 16384 rows on K of 1024 and more (mx_split_wins in
+// abi.hip), and the calls without a workspace never do.  Up to 32 tokens always,
+// up to 64 on up to 12288 rows (us per call, this kernel against the K ranges:
+// 4096x4096 at M = 1 / 16 /
 // 32 / 64: 4.9 / 5.0 / 5.6 / 7.7 against 8.6 / 9.7 / 10.8 / 14.0; 11008x4096
 // 8.4 / 8.6 / 11.0 / 18.5 against 13.2 / 14.8 / 16.4 / 19.6; 4096x11008 at M =
 // 16 / 64: 8.6 / 14.6 against 14.9 / 18.8; 4096x1024 at M = 16: 2.8 against
-// 7.4; 22016x4096 at M = 32 / 48 / 64: 24.2 / 37.9 / 39.6 against 25.1 / 28.6 /
-// 29.9).  Above, each 64 tokens expand the weights again, which pays while the
+// 7.4; 22016x4096, a path asked for by name, at M = 32 / 48 / 64: 24.2 / 37.9 /
+// 39.6 against 25.1 / 28.6 / 29.9).  Above, each 64 tokens expand the weights again, which pays while the
 // grid is at most two workgroups per CU on rows of up to 8192 K, or one on
 // longer ones (4096x4096 at M = 128: 13.9 against 20.8, M = 256, four per CU,
 // 24.5 against 26.7, M = 301 28 against 26; 1024x4096 at M = 256 / 512: 7.4 /

@@ -62,10 +62,11 @@ MFMA_PEAK = {"fp8": 5033.0, "f16": 2516.6, "fp4": 10066.0, "int8": 5033.0}
 
 
 def dual_mfma_peak() -> float:
-    """Dense-equivalent peak of the dual GEMM's instruction mix: per 64 K of a
+    """Dense-equivalent peak of the dual GEMM at dense rates: per 64 K of a
     32x32 tile one fp4 x fp4 instruction (32*32*64 products at the fp4 rate)
     and two int8 ones (32*32*32 each at the int8 rate); the dense-equivalent
-    work is 2*32*32*64."""
+    work is 2*32*32*64.  (The tiled kernel issues the int8 part as one 2:4
+    sparse instruction, which is not priced at the sparse rate here.)"""
     t = 2 * 32 * 32 * 64 / MFMA_PEAK["fp4"] + 2 * (2 * 32 * 32 * 32) / MFMA_PEAK["int8"]
     return 2 * 32 * 32 * 64 / t
 

@@ -36,13 +36,13 @@
 //
 // The activations of a 128-K chunk are staged in LDS once per workgroup in
 // three buffers (one barrier per chunk); weights stream into registers a
-// chunk and more ahead.  What bounds it: at 128 x 256 the matrix cores need
-// 1024 cycles per chunk, the LDS reads of the activations 770, the vector
-// memory address unit 1160 (a request of 64 lanes x 16 bytes takes it 17
-// cycles, one of 4 bytes a lane 9, one that touches 32 rows 62), and a chunk
-// takes 2500: MfmaUtil 33%.  LLaMA-7B gate 11008x4096 at M = 4096: 268 us
-// (dense int8 outliers, one wave per SIMD: 390); 4096x4096 at M = 256: 14.5
-// (28).
+// chunk and more ahead.  What bounds it, by counters on 11008x4096 at M = 4096
+// (128 x 256): a chunk takes a compute unit 2550 cycles, of which the matrix
+// cores are busy 1024 (MfmaUtil 39%), the LDS 800, the vector memory address
+// unit 1690 and its data path 1930 (76%; a request of 64 lanes x 16 bytes takes
+// the address unit 17 cycles, one of 4 bytes a lane 9, one that touches 32 rows
+// 62).  That layer: 268 us (dense int8 outliers, one wave per SIMD: 390);
+// 4096x4096 at M = 256: 14.5 (28).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

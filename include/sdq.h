@@ -340,7 +340,11 @@ sdq_status sdq_gemm_path_ws(const sdq_config* cfg, int64_t M, int64_t N, int64_t
  *          except for calls with K < 16384 that its kernel for few tokens
  *          takes without a workspace (up to 16 tokens; up to 64 while
  *          ceil(N/32) * ceil(M/32) <= 128; up to 32 with e4m3 outliers and N
- *          <= 12288); else what sdq_gemm takes
+ *          <= 12288) and whose rows are not long and few: up to 16 tokens N <=
+ *          1024 and K >= 8704 with e4m3 outliers and fp16 scales, K >= 10240
+ *          with one-byte scales, K >= 12288 with int8 outliers; up to 32 tokens
+ *          N <= 2048 and K >= 8192, above 32 N <= 1024 and K >= 8192, stay
+ *          SDQ_PATH_SPLITK; else what sdq_gemm takes
  *   bytes  32 * ceil(N / 32) * K for SDQ_PATH_DENSE; 4 * S * M * N for
  *          SDQ_PATH_SPLITK, with S (the number of K ranges, at most
  *          ceil(K / 128) / 4) chosen from M, N and K so that about 2048

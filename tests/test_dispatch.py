@@ -45,7 +45,20 @@ def test_every_kernel_of_the_dispatch_is_named_by_a_test():
                     "mx_small", "mx_mfma 32", "mx_mfma 64", "mx_mfma 128"}
 
 
+INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m3", 3, 8, "int4", "int8", sfmt_i="e4m3")
+
+
 @pytest.mark.parametrize("cfg,M,N,K,kernel", [
+    # long rows, few of them: the kernel for few tokens walks all of K in each
+    # workgroup, and leaves them to the K ranges
+    (INT, 16, 512, 11008, "int_split 32 (21 K ranges)"), (INT, 9, 1024, 8704, "int_split 32 (17 K ranges)"),
+    (INT, 9, 1024, 8672, "int_small"), (INT, 16, 1056, 13824, "int_small"),
+    (INT8S, 16, 1024, 8704, "int_small"), (INT8S, 16, 1024, 10240, "int_split 32 (20 K ranges)"),
+    (INT8O, 16, 512, 11008, "int_small"), (INT8O, 16, 512, 12288, "int_split 32 (24 K ranges)"),
+    (INT, 17, 2048, 8192, "int_split 32 (16 K ranges)"), (INT8O, 32, 1024, 11008, "int_split 32 (21 K ranges)"),
+    (INT, 32, 2080, 11008, "int_small"), (INT, 32, 2048, 8160, "int_small"),
+    (INT, 33, 512, 11008, "int_split 64 (21 K ranges)"), (INT8O, 64, 1024, 8192, "int_split 64 (16 K ranges)"),
+    (INT, 64, 1056, 11008, "int_small"), (INT, 64, 1024, 8160, "int_small"),
     (INT, 1, 4096, 4096, "int_decode"), (INT, 16, 4096, 4096, "int_small"), (INT, 64, 16384, 4096, "int_split 64 (4 K ranges)"),
     (INT, 201, 4096, 11008, "int_tiled 128 (8 K ranges)"), (INT, 2048, 4096, 4096, "int_tiled"),
     (MX, 1, 4096, 4096, "mx_small"), (MX, 301, 4096, 11008, "mx_mfma 128 (5 K ranges)"),

@@ -318,7 +318,8 @@ sdq_status sdq_gemm_path_ws(const sdq_config* cfg, int64_t M, int64_t N, int64_t
  * each workgroup converts its activations to the matrix instruction's f16 once
  * for four row tiles; in the MX family (up to a few hundred tokens) it is the
  * one-pass scaled-MFMA kernel over a range of K, so that a small grid still
- * fills the GPU.  With few tokens (always up to 32, more on small layers) the
+ * fills the GPU.  With few tokens (always up to 32, more on layers that are
+ * small or have short rows) the
  * MX family instead runs one kernel that splits K over the waves of a
  * workgroup and adds their sums there: the workspace is still required and
  * checked, and not written.

@@ -243,27 +243,35 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 
 // On SDQ_PATH_SPLITK alone, against the K ranges with their second pass; AUTO
 // takes that path up to 16384 rows on K of 1024 and more (mx_split_wins in
-// abi.hip), and the calls without a workspace never do.  Up to 32 tokens always,
-// up to 64 on up to 12288 rows (us per call, this kernel against the K ranges:
-// 4096x4096 at M = 1 / 16 /
+// abi.hip), and the calls without a workspace never do.  Up to 32 tokens always
+// (us per call, this kernel against the K ranges: 4096x4096 at M = 1 / 16 /
 // 32 / 64: 4.9 / 5.0 / 5.6 / 7.7 against 8.6 / 9.7 / 10.8 / 14.0; 11008x4096
 // 8.4 / 8.6 / 11.0 / 18.5 against 13.2 / 14.8 / 16.4 / 19.6; 4096x11008 at M =
 // 16 / 64: 8.6 / 14.6 against 14.9 / 18.8; 4096x1024 at M = 16: 2.8 against
-// 7.4; 22016x4096, a path asked for by name, at M = 32 / 48 / 64: 24.2 / 37.9 /
-// 39.6 against 25.1 / 28.6 / 29.9).  Above, each 64 tokens expand the weights again, which pays while the
+// 7.4).  Up to 64 tokens on up to 12288 rows (22016x4096, a path asked for by
+// name, at M = 48 / 64: 37.9 / 39.6 against 28.6 / 29.9) while rows are not
+// long: a workgroup walks all of K, so its time follows K alone while the grid
+// fits one round, where the K ranges' follows N too (M = 64, this kernel /
+// K ranges: 1024 rows at K = 6144 / 8192 / 11008: 10.4, 11.0 / 12.3, 11.7 / 16.1,
+// 13.5; 2048 rows at K = 11008 16.7, 18.6; 4096 rows at K = 11008 / 16000: 17.4,
+// 19.0 / 22.6, 21.1; 8192 rows at K = 4096 / 6144: 15.7, 16.2 / 20.3, 19.2).
+// Above, each 64 tokens expand the weights again, which pays while the
 // grid is at most two workgroups per CU on rows of up to 8192 K, or one on
 // longer ones (4096x4096 at M = 128: 13.9 against 20.8, M = 256, four per CU,
 // 24.5 against 26.7, M = 301 28 against 26; 1024x4096 at M = 256 / 512: 7.4 /
 // 12.8 against 14.6 / 19.8; 2048x8192 at M = 128 / 256: 11.8 / 20.0 against
 // 20.1 / 22.8; 4096x11008 at M = 128, two per CU: 27.7 against 24.7; 8192x2048
-// at M = 128, four: 16.4 against 14.1).  A wave's chain over a very long row
-// costs the same at 33 tokens as at 64 (1024x16384 at M = 33 / 64: 16.5 / 16.8
-// against 15.4 / 17.3).
+// at M = 128, four: 16.4 against 14.1), and on longer rows while the grid is
+// not so small that the K ranges are the fuller one (M = 128: 256 rows, 32
+// workgroups, at K = 11008 / 16000: 14.2, 13.4 / 18.8, 15.5; 512 rows 14.5, 14.3
+// / 19.2, 17.2; 1024 rows, 128 workgroups, at K = 16000 20.7, 19.1; 2048 rows at
+// K = 16000 / 20480: 21.2, 22.7 / 26.3, 25.5).
 bool mx_small_wins(int64_t M, int64_t N, int64_t K) {
   if (M <= 32) return true;
-  if (M <= 64) return N <= 12288 && (K <= 12288 || M > 48);
+  if (M <= 64) return N <= 4096 ? K < 8192 || (K <= 12288 && N > 1536) : N <= 12288 && K <= 5120;
   const int64_t wgs = (N + kSmallRows - 1) / kSmallRows * ((M + 63) / 64);
-  return wgs <= (K <= 8192 ? 512 : 256);
+  if (K <= 8192) return wgs <= 512;
+  return wgs <= 256 && wgs >= (K <= 14336 ? 64 : K <= 16384 ? 160 : 256);
 }
 
 hipError_t launch_mx_small(const Cfg& c, const uint8_t* Xq, const float* s_a, int64_t M, const uint8_t* blob,

@@ -59,6 +59,13 @@ INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m
     (INT, 32, 2080, 11008, "int_small"), (INT, 32, 2048, 8160, "int_small"),
     (INT, 33, 512, 11008, "int_split 64 (21 K ranges)"), (INT8O, 64, 1024, 8192, "int_split 64 (16 K ranges)"),
     (INT, 64, 1056, 11008, "int_small"), (INT, 64, 1024, 8160, "int_small"),
+    # (MX: above 32 tokens alike)
+    (MX, 32, 1024, 16000, "mx_small"), (MX, 33, 1024, 8160, "mx_small"), (MX, 64, 1024, 8192, "mx_mfma 64 (16 K ranges)"),
+    (MX, 64, 1536, 11008, "mx_mfma 64 (18 K ranges)"), (MX, 64, 1568, 12288, "mx_small"),
+    (MX, 64, 2048, 12320, "mx_mfma 64 (20 K ranges)"), (MX, 64, 8192, 5120, "mx_small"),
+    (MX, 64, 8192, 5152, "mx_mfma 64 (7 K ranges)"), (MX, 128, 256, 11008, "mx_mfma 128 (18 K ranges)"),
+    (MX, 128, 512, 11008, "mx_small"), (MX, 128, 1024, 16000, "mx_mfma 128 (25 K ranges)"),
+    (MX, 192, 1024, 16000, "mx_small"), (MX, 128, 256, 8192, "mx_small"),
     (INT, 1, 4096, 4096, "int_decode"), (INT, 16, 4096, 4096, "int_small"), (INT, 64, 16384, 4096, "int_split 64 (4 K ranges)"),
     (INT, 201, 4096, 11008, "int_tiled 128 (8 K ranges)"), (INT, 2048, 4096, 4096, "int_tiled"),
     (MX, 1, 4096, 4096, "mx_small"), (MX, 301, 4096, 11008, "mx_mfma 128 (5 K ranges)"),

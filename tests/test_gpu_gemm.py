@@ -452,7 +452,7 @@ def test_split_k_ragged_shapes(c, M, N, K):
 
 
 MX_SPLITK = [  # M, N, K, kernel
-    (9, 4128, 512, "mx_small"), (33, 97, 4096, "mx_small"), (64, 1000, 16384, "mx_small"), (100, 544, 1152, "mx_small"),
+    (9, 4128, 512, "mx_small"), (33, 97, 4096, "mx_small"), (64, 1000, 16384, "mx_mfma 64 (32 K ranges)"), (64, 1000, 8160, "mx_small"), (64, 2100, 12288, "mx_small"), (100, 544, 1152, "mx_small"),
     (129, 64, 8192, "mx_small"), (511, 33, 1024, "mx_small"),
     (50, 12400, 1184, "mx_mfma 64 (2 K ranges)"), (64, 16384, 1024, "mx_mfma 64 (2 K ranges)"),
     (33, 1000, 16384, "mx_mfma 64 (32 K ranges)"),

@@ -18,7 +18,7 @@ INT, MX = sdq.Config.int_family(), sdq.Config.mx_family()
 
 @pytest.mark.parametrize("cfg,M,N,K", [(INT, 1, 256, 512), (INT, 16, 256, 512), (INT, 64, 8192, 256),
                                        (INT, 33, 96, 8192), (INT, 16, 96, 8704), (INT, 20, 96, 8192), (MX, 1, 96, 256), (MX, 5, 96, 1024),
-                                       (MX, 600, 10240, 256)])
+                                       (MX, 48, 96, 8192), (MX, 600, 10240, 256)])
 def test_linear_equals_quantize_then_gemm(cfg, M, N, K):
     torch = torch_cuda()
     say("linear ws", cfg.label, M, N, K)

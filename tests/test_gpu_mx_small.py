@@ -11,7 +11,7 @@ import pytest
 
 import synth
 from oracle import sdq as S
-from tests.gpu_util import assert_close_terms, say, torch_cuda
+from tests.gpu_util import assert_close_terms, kernel_of, say, torch_cuda
 
 import paper_2406_13868_amd as sdq
 
@@ -19,13 +19,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 33, 128), (9, 48, 96), (16, 4100, 4096), (17, 15, 2176), (32, 130, 4768),
-                                   (33, 96, 1024), (64, 2048, 256), (50, 100, 9344), (5, 64, 5120),
+                                   (33, 96, 1024), (64, 2048, 256), (50, 100, 8160), (50, 1640, 9344), (5, 64, 5120),
                                    (65, 72, 1184), (130, 512, 640)])
 @pytest.mark.parametrize("n_o,n_i,split", [(1, 2, False), (1, 3, True), (0, 3, False), (1, 1, False)])
 def test_few_tokens_match_oracle(M, N, K, n_o, n_i, split):
     torch = torch_cuda()
     cfg = sdq.Config("mx", n_o, 8, "e4m3", n_i, 8, "e2m1", "e4m3")
     cfg_o = S.Config("mx", n_o, 8, "e4m3", n_i, 8, "e2m1", "e4m3")
+    assert kernel_of(cfg, M, N, K, sdq.PATH_SPLITK) == "mx_small"
     X, W = synth.make_x(2, M, K), synth.make_w(2, 0, N, K)
     if split:  # a few blocks whose outliers are far above their inliers
         W[::3, 0:8 * (K // 8):40] = 60000.0

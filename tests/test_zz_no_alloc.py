@@ -69,7 +69,8 @@ def test_static_entry_refuses_a_workspace_beyond_the_array():
 
 STATIC_SPLITK = [  # family, two shapes (M, N, K, kernel), the second smaller
     ("int", (64, 4128, 16384, "int_split 64 (16 K ranges)"), (20, 1000, 2048, "int_split 32 (4 K ranges)")),
-    ("mx", (64, 4128, 16384, "mx_small"), (20, 1000, 2048, "mx_small")),
+    ("mx", (64, 4128, 4096, "mx_small"), (20, 1000, 2048, "mx_small")),
+    ("mx", (64, 4128, 16384, "mx_mfma 64 (15 K ranges)"), (20, 1000, 2048, "mx_small")),
     ("mx", (256, 4096, 4096, "mx_mfma 128 (8 K ranges)"), (300, 2080, 1152, "mx_mfma 128 (2 K ranges)")),
 ]
 

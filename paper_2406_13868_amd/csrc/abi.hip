@@ -111,7 +111,7 @@ void kernel_name(const Cfg& c, int32_t path, int64_t M, int64_t N, int64_t K, ch
   if (c.dual) {
     const char* const names[] = {"dual_decode",       "dual_splitk",       "dual_tiled 32x128",
                                  "dual_tiled 64x128", "dual_tiled 64x256", "dual_tiled 128x256"};
-    std::snprintf(out, n, "%s", names[int(dual_form(M, N, K))]);
+    std::snprintf(out, n, "%s", names[int(dual_form(M, N, K, c.n_o))]);
   } else if (path == SDQ_PATH_DENSE) {
     std::snprintf(out, n, "mx_dense (two passes)");
   } else if (path == SDQ_PATH_SPLITK && c.mx && mx_small_wins(M, N, K)) {

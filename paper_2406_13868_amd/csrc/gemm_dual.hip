@@ -657,10 +657,16 @@ hipError_t launch_np(DualForm f, const DualArgs& a, hipStream_t st) {
 }  // namespace
 
 // The split-K form while its grid (one tile x 32 tokens per workgroup) stays
-// within one round, and up to 8 tokens: its waves gather activation rows
-// themselves, which costs by the row (4096x4096 at M = 16 / 64: 9.4 / 12.7 us
-// against 12.2 / 12.6 in tiles; 11008x4096, 344 workgroups, at M = 4 / 16 /
-// 32: 11.7 / 15.9 / 21.7 against 12.4 / 12.5 / 13.2).  Else the tiled form
+// within one round, and on wider layers up to 12 tokens (16 with two outlier
+// planes, whose expansion weighs more in the tiled form): its waves gather
+// activation rows themselves, which costs by the row (4096x4096 at M = 16 / 64:
+// 9.4 / 12.7 us against 12.2 / 12.6 in tiles; 11008x4096, 344 workgroups, at M =
+// 9 / 16 / 32, weights from memory: 15.0 / 17.0 / 24.2 against 16.0 / 16.4 /
+// 18.5, with two planes 17.4 / 18.7 / 26.1 against 19.5 / 20.1 / 22.6); and up to
+// 24 tokens on rows of up to 768 and 32 on 512, where a tile's prologue is most
+// of its time (11008x512 at M = 9 / 16 / 32: 5.6 / 5.9 / 6.8 against 6.6 / 6.6 /
+// 7.0; 8224x768 at M = 16 / 24: 6.6 / 7.2 against 7.3 / 7.4; 11008x1024 at M = 9 /
+// 16 / 32 8.3 / 9.1 / 11.6 against 8.2 / 8.4 / 9.0).  Else the tiled form
 // of least cost, with these costs of a round of 256 workgroups in half
 // microseconds at K = 4096 (other K scale alike): 32 tokens x 128 outputs 27;
 // 64 x 128 33, and 24 for each further round (two run per CU); 64 x 256 46;
@@ -669,11 +675,12 @@ hipError_t launch_np(DualForm f, const DualArgs& a, hipStream_t st) {
 // 28.2, 35.6 / -, 60.7, 55.6, 46.0; 11008x4096 at M = 128 / 256 / 512: 24.9,
 // 17.7, 21.9, 29.6 / 37.2, 27.7, 24.4, 31.5 / 71.0, 42.5, 46.3, 36.7;
 // 4096x11008 at M = 256 / 768: 28.8, 35.8, 45.9, 63.6 / 81.2, 66.1, 52.8, 68.7.
-DualForm dual_form(int64_t M, int64_t N, int64_t K) {
+DualForm dual_form(int64_t M, int64_t N, int64_t K, int planes) {
   if (dual_decode_fits(M, N, K)) return DualForm::kDecode;
   const int64_t tiles = (N + kTileN - 1) / kTileN;
-  // (the tiled form's first scales are read 16 bytes at a time)
-  if (M <= 8 || tiles * ((M + 31) / 32) <= 256 || M * (K / 32) < 16) return DualForm::kSplitK;
+  // (what is left has the 16 bytes of scales that the tiled form's first requests take)
+  if (M <= (planes == 2 ? 16 : 12) || (M <= 24 && K <= 768) || (M <= 32 && K <= 512) || tiles * ((M + 31) / 32) <= 256)
+    return DualForm::kSplitK;
   const int64_t g4 = (tiles + 3) / 4, g8 = (tiles + 7) / 8;
   const auto rounds = [](int64_t wgs) { return (wgs + 255) / 256; };
   const int64_t c11 = 27 * rounds(g4 * ((M + 31) / 32)), c21 = 9 + 24 * rounds(g4 * ((M + 63) / 64));
@@ -691,7 +698,7 @@ hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, c
              L.out_off, L.scale_off, L.rows_off};
   a.y_bf16 = c.y_bf16;
   a.y_vec = out_vec(Y, N);
-  const DualForm f = dual_form(M, N, K);
+  const DualForm f = dual_form(M, N, K, L.out_planes);
   if (f == DualForm::kDecode) return launch_dual_decode(c, Xo, s_a, Xi, Ea, M, blob, N, K, Y, st);
   return L.out_planes == 2 ? launch_np<2>(f, a, st) : launch_np<1>(f, a, st);
 }

@@ -65,7 +65,7 @@ hipError_t launch_dual_decode(const Cfg& c, const uint8_t* Xo, const float* s_a,
 // Dual family (any M): the decode kernel, or the matrix-core kernel (fp4 x fp4
 // inliers and int8 x int8 outliers) in the form dual_form names.
 enum class DualForm { kDecode, kSplitK, k32x128, k64x128, k64x256, k128x256 };
-DualForm dual_form(int64_t M, int64_t N, int64_t K);
+DualForm dual_form(int64_t M, int64_t N, int64_t K, int planes);  // outlier planes (1 or 2)
 hipError_t launch_dual_mfma(const Cfg& c, const uint8_t* Xo, const float* s_a, const uint8_t* Xi,
                             const uint8_t* Ea, int64_t M, const uint8_t* blob, int64_t N, int64_t K,
                             void* Y, hipStream_t st);

@@ -19,7 +19,7 @@ def _cases():
     for M, N, K, kernel in dual.FORMS + dual_tiled.NAN_SHAPES:
         yield DUAL, M, N, K, sdq.PATH_AUTO, kernel
     for M, N, K, form in dual_tiled.SHAPES:
-        yield DUAL, M, N, K, sdq.PATH_AUTO, f"dual_tiled {form}"
+        yield DUAL, M, N, K, sdq.PATH_AUTO, dual_tiled.kernel_name(form)
     for fam, M, N, K, kernel in gemm.KERNELS_ABOVE_64 + partial.KERNELS:
         yield INT if fam == "int" else MX, M, N, K, sdq.PATH_MFMA, kernel
     for M, N, K, fmt_o, kernel in gemm.INT_32_ROWS:
@@ -45,6 +45,7 @@ def test_every_kernel_of_the_dispatch_is_named_by_a_test():
                     "mx_small", "mx_mfma 32", "mx_mfma 64", "mx_mfma 128"}
 
 
+DUAL2 = sdq.Config("dual", 2, 8, "int8", 4, 8, "e2m1", "int8")
 INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m3", 3, 8, "int4", "int8", sfmt_i="e4m3")
 
 
@@ -66,6 +67,11 @@ INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m
     (MX, 64, 8192, 5152, "mx_mfma 64 (7 K ranges)"), (MX, 128, 256, 11008, "mx_mfma 128 (18 K ranges)"),
     (MX, 128, 512, 11008, "mx_small"), (MX, 128, 1024, 16000, "mx_mfma 128 (25 K ranges)"),
     (MX, 192, 1024, 16000, "mx_small"), (MX, 128, 256, 8192, "mx_small"),
+    # dual: the split-K form for few tokens on wide layers
+    (DUAL, 12, 11008, 4096, "dual_splitk"), (DUAL, 13, 11008, 4096, "dual_tiled 32x128"),
+    (DUAL2, 16, 11008, 4096, "dual_splitk"), (DUAL2, 17, 11008, 4096, "dual_tiled 32x128"),
+    (DUAL, 24, 8224, 768, "dual_splitk"), (DUAL, 24, 8224, 800, "dual_tiled 32x128"),
+    (DUAL, 32, 11008, 512, "dual_splitk"), (DUAL, 25, 11008, 544, "dual_tiled 32x128"),
     (INT, 1, 4096, 4096, "int_decode"), (INT, 16, 4096, 4096, "int_small"), (INT, 64, 16384, 4096, "int_split 64 (4 K ranges)"),
     (INT, 201, 4096, 11008, "int_tiled 128 (8 K ranges)"), (INT, 2048, 4096, 4096, "int_tiled"),
     (MX, 1, 4096, 4096, "mx_small"), (MX, 301, 4096, 11008, "mx_mfma 128 (5 K ranges)"),

@@ -2,7 +2,8 @@
 each of its workgroup shapes, against the fp64 oracle.
 
 The launcher picks the shape by grid: 32 tokens x 128 outputs (two K groups
-per workgroup), 64 x 128, 64 x 256 and 128 x 256.  For each: ragged tokens
+per workgroup), 64 x 128, 64 x 256 and 128 x 256 (and leaves few tokens on
+short rows to the split-K form).  For each: ragged tokens
 and outputs, one chunk of K, an odd number of chunks, more chunks than the
 buffers of the staging loop hold, K that is not a whole chunk (with rows of
 scales that are not whole dwords), one and two outlier planes, fp32 and bf16 outputs, an output that is not 16-byte aligned.  The
@@ -21,8 +22,9 @@ import paper_2406_13868_amd as sdq
 pytestmark = pytest.mark.gpu
 
 SHAPES = [  # M, N, K, form
-    (9, 8225, 160, "32x128"), (16, 8224, 32, "32x128"), (32, 8200, 416, "32x128"), (33, 8193, 128, "32x128"),
-    (40, 8200, 1152, "32x128"),
+    (9, 8225, 160, "splitk"), (16, 8224, 32, "splitk"), (32, 8200, 416, "splitk"),  # (few tokens on short rows)
+    (33, 8225, 160, "32x128"), (34, 8224, 32, "32x128"), (64, 8200, 416, "32x128"), (33, 8193, 128, "32x128"),
+    (25, 8225, 544, "32x128"), (40, 8200, 1152, "32x128"),
     (130, 8196, 96, "64x128"), (321, 4129, 288, "64x128"), (384, 4096, 640, "64x128"), (1100, 8193, 96, "64x128"),
     (2049, 4100, 416, "64x128"), (321, 4129, 128, "64x128"), (321, 4129, 1152, "64x128"),
     (700, 4100, 256, "64x256"), (700, 4100, 96, "64x256"), (700, 4100, 288, "64x256"), (700, 4100, 416, "64x256"),
@@ -32,13 +34,17 @@ SHAPES = [  # M, N, K, form
 ]
 
 
+def kernel_name(form):
+    return "dual_splitk" if form == "splitk" else f"dual_tiled {form}"
+
+
 @pytest.mark.parametrize("n_o,n_i", [(1, 6), (2, 4)])
 @pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M,N,K,form", SHAPES)
 def test_tiled_shapes_match_oracle(M, N, K, form, n_o, n_i, y_dtype):
     torch = torch_cuda()
     cfg = sdq.Config("dual", n_o, 8, "int8", n_i, 8, "e2m1", "int8", y_dtype=y_dtype)
-    assert kernel_of(cfg, M, N, K) == f"dual_tiled {form}"
+    assert kernel_of(cfg, M, N, K) == kernel_name(form)
     cfg_o = S.Config("dual", n_o, 8, "int8", n_i, 8, "e2m1", "int8+e2m1")
     X, W = synth.make_x(2, M, K), synth.make_w(2, 0, N, K)
     X[M // 2] = 0.0  # an all-zero token
@@ -66,7 +72,8 @@ def test_tiled_shapes_match_oracle(M, N, K, form, n_o, n_i, y_dtype):
 
 NAN_SHAPES = [  # M, N, K, kernel
     (16, 256, 160, "dual_splitk"),
-    (32, 8200, 160, "dual_tiled 32x128"), (32, 8200, 384, "dual_tiled 32x128"),  # (384: an odd number of chunks)
+    (32, 8200, 160, "dual_splitk"), (32, 8200, 384, "dual_splitk"),
+    (40, 8200, 160, "dual_tiled 32x128"), (40, 8200, 384, "dual_tiled 32x128"),  # (384: an odd number of chunks)
     (32, 8200, 1152, "dual_tiled 32x128"), (32, 8200, 1408, "dual_tiled 32x128"), (40, 8200, 1184, "dual_tiled 32x128"),
     (321, 4129, 160, "dual_tiled 64x128"), (700, 4100, 160, "dual_tiled 64x256"), (513, 8225, 160, "dual_tiled 128x256"),
     (321, 4129, 672, "dual_tiled 64x128"), (700, 4100, 672, "dual_tiled 64x256"), (513, 8225, 1184, "dual_tiled 128x256"),

@@ -344,7 +344,8 @@ sdq_status sdq_gemm_path_ws(const sdq_config* cfg, int64_t M, int64_t N, int64_t
  *          <= 12288) and whose rows are not long and few: up to 16 tokens N <=
  *          1024 and K >= 8704 with e4m3 outliers and fp16 scales, K >= 10240
  *          with one-byte scales, K >= 12288 with int8 outliers; up to 32 tokens
- *          N <= 2048 and K >= 8192, above 32 N <= 1024 and K >= 8192, stay
+ *          N <= 1536 and K >= 8192, or N <= 2048 and K >= 12288; above 32 N <=
+ *          1024 and K >= 8192, with one-byte scales 10240, stay
  *          SDQ_PATH_SPLITK; else what sdq_gemm takes
  *   bytes  32 * ceil(N / 32) * K for SDQ_PATH_DENSE; 4 * S * M * N for
  *          SDQ_PATH_SPLITK, with S (the number of K ranges, at most

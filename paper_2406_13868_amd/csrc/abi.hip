@@ -58,13 +58,16 @@ int32_t auto_path(const Cfg& c, int64_t M, int64_t K) {
 // on long rows where N is small (N = 1024, small-M kernel / K ranges: K = 8192
 // at M = 16 / 32 / 64: 12.3, 12.5 / 15.2, 12.9 / 15.1, 15.0; K = 11008: 16.2,
 // 15.6 / 20.0, 15.5 / 19.7, 17.6; K = 16000: 21.6, 18.1 / 26.7, 18.9 / 26.5,
-// 21.8; N = 2048, K = 16000: 21.9, 22.2 / 27.0, 23.4 / 26.7, 26.7; at M = 16, N =
-// 1024, K = 9216 14.1, 13.4, with one-byte scales 13.6, 14.0, and with int8
-// outliers at K = 11008 / 13824 13.9, 15.1 / 16.2, 16.1).
+// 21.8; N = 2048 at M = 32, K = 9216 / 16000: 17.6, 18.8 / 27.0, 23.4; at M = 16,
+// N = 1024, K = 9216 14.1, 13.4, with one-byte scales 13.6, 14.0 (M = 64, K = 8192
+// 15.0, 16.5), and with int8 outliers at K = 11008 / 13824 13.9, 15.1 / 16.2,
+// 16.1).
 bool split_wins(const Cfg& c, int64_t M, int64_t N, int64_t K) {
   if (M <= 64 && K < 16384 && int_small_wins(c, M, N)) {
-    if (M <= 16) return N <= 1024 && K >= (c.fmt_o == SDQ_FMT_INT8 ? 12288 : c.scale_bytes() == 2 ? 8704 : 10240);
-    return N <= (M <= 32 ? 2048 : 1024) && K >= 8192;
+    const bool byte_scales = c.scale_bytes() == 1;
+    if (M <= 16) return N <= 1024 && K >= (c.fmt_o == SDQ_FMT_INT8 ? 12288 : byte_scales ? 10240 : 8704);
+    if (M <= 32) return N <= (K >= 12288 ? 2048 : 1536) && K >= 8192;
+    return N <= 1024 && K >= (byte_scales ? 10240 : 8192);
   }
   if (M > kSplitMaxM) return K >= 1024 && (N + 127) / 128 * ((M + 127) / 128) < 384;
   return K >= 8192 || (M >= 64 && N >= 8192) || M >= 256;

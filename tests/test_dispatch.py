@@ -56,8 +56,10 @@ INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m
     (INT, 9, 1024, 8672, "int_small"), (INT, 16, 1056, 13824, "int_small"),
     (INT8S, 16, 1024, 8704, "int_small"), (INT8S, 16, 1024, 10240, "int_split 32 (20 K ranges)"),
     (INT8O, 16, 512, 11008, "int_small"), (INT8O, 16, 512, 12288, "int_split 32 (24 K ranges)"),
-    (INT, 17, 2048, 8192, "int_split 32 (16 K ranges)"), (INT8O, 32, 1024, 11008, "int_split 32 (21 K ranges)"),
-    (INT, 32, 2080, 11008, "int_small"), (INT, 32, 2048, 8160, "int_small"),
+    (INT, 17, 1536, 8192, "int_split 32 (16 K ranges)"), (INT, 17, 1568, 8192, "int_small"),
+    (INT, 32, 2048, 12288, "int_split 32 (24 K ranges)"), (INT8S, 64, 1024, 10208, "int_small"),
+    (INT8S, 64, 1024, 10240, "int_split 64 (20 K ranges)"), (INT8O, 32, 1024, 11008, "int_split 32 (21 K ranges)"),
+    (INT, 32, 2080, 13824, "int_small"), (INT, 32, 2048, 8160, "int_small"),
     (INT, 33, 512, 11008, "int_split 64 (21 K ranges)"), (INT8O, 64, 1024, 8192, "int_split 64 (16 K ranges)"),
     (INT, 64, 1056, 11008, "int_small"), (INT, 64, 1024, 8160, "int_small"),
     # (MX: above 32 tokens alike)

@@ -253,8 +253,9 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 // long: a workgroup walks all of K, so its time follows K alone while the grid
 // fits one round, where the K ranges' follows N too (M = 64, this kernel /
 // K ranges: 1024 rows at K = 6144 / 8192 / 11008: 10.4, 11.0 / 12.3, 11.7 / 16.1,
-// 13.5; 2048 rows at K = 11008 16.7, 18.6; 4096 rows at K = 11008 / 16000: 17.4,
-// 19.0 / 22.6, 21.1; 8192 rows at K = 4096 / 6144: 15.7, 16.2 / 20.3, 19.2).
+// 13.5; 2048 rows at K = 11008 / 13824: 16.7, 18.6 / 19.5, 20.6; 4096 rows at K =
+// 11008 / 16000: 17.4, 19.0 / 22.6, 21.1; 8192 rows at K = 4096 / 6144: 15.7, 16.2
+// / 20.3, 19.2).
 // Above, each 64 tokens expand the weights again, which pays while the
 // grid is at most two workgroups per CU on rows of up to 8192 K, or one on
 // longer ones (4096x4096 at M = 128: 13.9 against 20.8, M = 256, four per CU,
@@ -268,7 +269,7 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 // K = 16000 / 20480: 21.2, 22.7 / 26.3, 25.5).
 bool mx_small_wins(int64_t M, int64_t N, int64_t K) {
   if (M <= 32) return true;
-  if (M <= 64) return N <= 4096 ? K < 8192 || (K <= 12288 && N > 1536) : N <= 12288 && K <= 5120;
+  if (M <= 64) return N <= 4096 ? K < 8192 || (K <= (M <= 48 ? 12288 : 14336) && N > 1536) : N <= 12288 && K <= 5120;
   const int64_t wgs = (N + kSmallRows - 1) / kSmallRows * ((M + 63) / 64);
   if (K <= 8192) return wgs <= 512;
   return wgs <= 256 && wgs >= (K <= 14336 ? 64 : K <= 16384 ? 160 : 256);

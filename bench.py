@@ -423,6 +423,10 @@ def measure(a, torch, sdq, workload, M_arg, full, scale=("", 0)):
     y_bytes = 2 if cfg.y_dtype == "bf16" else 4
     alg_bytes = logical + sum(M * L.K + 4 * M + y_bytes * M * L.N for L in Ls)
     paths = [] if dual else sorted({sdq.gemm_path(cfg, M, L.N, L.K, workspace=True) for L in Ls})
+    # (the MX family's kernel for few tokens, on the split-K path, is one kernel)
+    few = sdq.PATH_SPLITK in paths and all(
+        sdq._lib.kernel_name(cfg.c(), M, L.N, L.K, sdq.PATH_SPLITK) == "mx_small" for L in Ls
+        if sdq.gemm_path(cfg, M, L.N, L.K, workspace=True) == sdq.PATH_SPLITK)
     hbm_bound = cfg.family == "int" and M <= 64 or (cfg.family != "int" and M < 256)
     tkey = workload if workload != "sweep" else f"sweep_l{a.layer}_m{M}_f{a.fmt}"
     if wid == 6 and a.fmt:
@@ -466,7 +470,7 @@ def measure(a, torch, sdq, workload, M_arg, full, scale=("", 0)):
                               if tr else None)
     roof["kernel_us"] = round(gemm_us / len(Ls), 3)
     # kernels per GEMM call: a two-pass path's time is both passes together
-    roof["kernels_per_call"] = 2 if (sdq.PATH_DENSE in paths or sdq.PATH_SPLITK in paths) else 1
+    roof["kernels_per_call"] = 2 if sdq.PATH_DENSE in paths or (sdq.PATH_SPLITK in paths and not few) else 1
     roof["timing"] = (f"HIP events around a graph replay of {n_g} GEMM calls over {R} rotated copies, "
                       "after a 512 MB fill; median of three replays after two untimed ones")
 
@@ -498,7 +502,7 @@ def measure(a, torch, sdq, workload, M_arg, full, scale=("", 0)):
         "config": {"workload": wl_name, "M": M, "layers": [[L.name, L.N, L.K] for L in Ls],
                    "formats": fmt.label,
                    "gemm_path": "dual mfma" if dual else ", ".join(
-                       ["decode", "mfma", "dense (two passes)", "split-K (two passes)"][p - 1] for p in paths),
+                       ["decode", "mfma", "dense (two passes)", "split-K (one kernel)" if few else "split-K (two passes)"][p - 1] for p in paths),
                    "activations_quantized": [L.name for j, L in enumerate(Ls) if j not in shared],
                    "parallelism": "none (one GPU)"},
         "roofline": roof,

@@ -129,6 +129,16 @@ def lib() -> C.CDLL:
     return _lib
 
 
+def kernel_name(cfg: "sdq_config", M: int, N: int, K: int, path: int = PATH_AUTO) -> str:
+    """The kernel that a call takes on a path (AUTO: what the entry points
+    choose with a workspace), by the launchers' own rules: for tests and logs."""
+    out = C.create_string_buffer(64)
+    fn = lib().sdq_kernel_name
+    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_int32, C.c_char_p, C.c_size_t]
+    check(fn(C.byref(cfg), M, N, K, path, out, len(out)), "sdq_kernel_name")
+    return out.value.decode()
+
+
 def check(status: int, what: str) -> None:
     if status != SDQ_OK:
         raise SDQError(status, what)

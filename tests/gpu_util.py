@@ -52,14 +52,8 @@ def say(*a):
 def kernel_of(cfg, M: int, N: int, K: int, path: int = 0) -> str:
     """The kernel that a call takes on a path (0: what the entry points choose
     with a workspace), by the launchers' own rules."""
-    import ctypes as C
-
     from paper_2406_13868_amd import _lib
-    out = C.create_string_buffer(64)
-    fn = _lib.lib().sdq_kernel_name
-    fn.restype, fn.argtypes = C.c_int, [C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_int32, C.c_char_p, C.c_size_t]
-    assert fn(C.byref(cfg.c()), M, N, K, path, out, len(out)) == 0
-    return out.value.decode()
+    return _lib.kernel_name(cfg.c(), M, N, K, path)
 
 
 def rel_errors(Y: np.ndarray, Yref: np.ndarray):

@@ -321,6 +321,16 @@ def _same_device(first, *ts):
             raise ValueError(f"tensors are on different devices: {sorted(map(str, devs))}")
 
 
+def _workspace(nbytes: int, device, stream):
+    """A fresh workspace of one call: kept from reuse until the stream that the
+    call runs on is done with it, where that is not the current one."""
+    torch = _torch()
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if stream is not None:
+        ws.record_stream(stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream))
+    return ws
+
+
 def _out(out, M: int, N: int, cfg: Config, device):
     """The GEMM output: `out` checked against [M, N] of cfg's output dtype, or a new tensor."""
     dt = cfg.y_torch_dtype()
@@ -427,8 +437,7 @@ def gemm(Xq, s_a, packed, N: int, K: int, cfg: Config, out=None, path: int = PAT
                                           _dev(packed, "packed"), N, K, _dev(Y, "Y"),
                                           _stream(stream), path), "sdq_gemm")
         return Y
-    ws = workspace if workspace is not None else torch.empty(ws_bytes, dtype=torch.uint8,
-                                                             device=Xq.device)
+    ws = workspace if workspace is not None else _workspace(ws_bytes, Xq.device, stream)
     _need_bytes(ws, ws_bytes, "workspace")
     _lib.check(_lib.lib().sdq_gemm_ws(cfg._ref, _dev(Xq, "Xq"), _dev(s_a, "s_a"), M,
                                       _dev(packed, "packed"), N, K, _dev(Y, "Y"),
@@ -521,7 +530,7 @@ def linear(X, packed, N: int, K: int, cfg: Config, out=None, xq=None, scales=Non
         rc = _lib.lib().sdq_linear_ws(*args, None, 0, st)
     if rc == _lib.ERR_BUFFER_TOO_SMALL:  # the path takes a workspace and none that serves was given
         need = gemm_workspace_size(cfg, M, N, K)
-        ws = torch.empty(need, dtype=torch.uint8, device=X.device) if workspace is None else workspace
+        ws = _workspace(need, X.device, stream) if workspace is None else workspace
         _need_bytes(ws, need, "workspace")
         rc = _lib.lib().sdq_linear_ws(*args, _dev(ws, "workspace"), ws.nbytes, st)
     _lib.check(rc, "sdq_linear")

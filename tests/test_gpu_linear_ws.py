@@ -37,6 +37,45 @@ def test_linear_equals_quantize_then_gemm(cfg, M, N, K):
             sdq.linear(X, blob, N, K, cfg, workspace=torch.empty(nb - 16, dtype=torch.uint8, device="cuda"))
 
 
+@pytest.mark.parametrize("call", ["linear", "gemm"])
+def test_a_calls_own_workspace_outlives_another_stream(call, monkeypatch):
+    """A workspace that the call allocates is not given out again while the
+    stream that the call was sent to may still use it."""
+    torch = torch_cuda()
+    M, N, K = 33, 96, 8192
+    X = torch.from_numpy(synth.make_x(2, M, K)).cuda()
+    blob = torch.from_numpy(sdq.pack(synth.make_w(2, 0, N, K), INT)).cuda()
+    Xq, s_a = sdq.quantize_act(X, INT)
+    nb = sdq.gemm_workspace_size(INT, M, N, K)
+    want = sdq.gemm(Xq, s_a, blob, N, K, INT)
+    out = torch.empty_like(want)
+    q2, s2 = torch.empty_like(Xq), torch.empty_like(s_a)
+    side, taken, empty = torch.cuda.Stream(), [], torch.empty
+    torch.cuda.synchronize()
+
+    def record(*a, **k):
+        t = empty(*a, **k)
+        taken.append((t.data_ptr(), t.nbytes))
+        return t
+
+    say("own workspace on a side stream", call)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)  # cycles; the call's kernels wait behind it
+    monkeypatch.setattr(torch, "empty", record)
+    if call == "linear":
+        sdq.linear(X, blob, N, K, INT, out=out, xq=q2, scales=s2, stream=side)
+    else:
+        sdq.gemm(Xq, s_a, blob, N, K, INT, out=out, stream=side)
+    monkeypatch.undo()
+    (ptr, size), = taken
+    assert size == nb and nb > 0
+    other = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    assert not side.query(), "the side stream should still be asleep"
+    assert other.data_ptr() != ptr
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+
+
 def test_a_used_config_copies_and_pickles():
     cfg = sdq.Config.int_family()
     assert sdq.pack_size(cfg, 64, 256) == sdq.pack_size(cfg, 64, 256)

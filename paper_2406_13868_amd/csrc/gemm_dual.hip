@@ -38,7 +38,7 @@
 // three buffers (one barrier per chunk); weights stream into registers a
 // chunk and more ahead.  What bounds it, by counters on 11008x4096 at M = 4096
 // (128 x 256): a chunk takes a compute unit 2550 cycles, of which the matrix
-// cores are busy 1024 (MfmaUtil 39%), the LDS 800, the vector memory address
+// cores are busy 1024 (MfmaUtil 37-39%), the LDS 800, the vector memory address
 // unit 1690 and its data path 1930 (76%; a request of 64 lanes x 16 bytes takes
 // the address unit 17 cycles, one of 4 bytes a lane 9, one that touches 32 rows
 // 62).  That layer: 268 us (dense int8 outliers, one wave per SIMD: 390);

@@ -246,7 +246,7 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 // abi.hip), and the calls without a workspace never do.  Up to 32 tokens always
 // (us per call, this kernel against the K ranges: 4096x4096 at M = 1 / 16 /
 // 32 / 64: 4.9 / 5.0 / 5.6 / 7.7 against 8.6 / 9.7 / 10.8 / 14.0; 11008x4096
-// 8.4 / 8.6 / 11.0 / 18.5 against 13.2 / 14.8 / 16.4 / 19.6; 4096x11008 at M =
+// at M = 1 / 16 / 32 8.4 / 8.6 / 11.0 against 13.2 / 14.8 / 16.4; 4096x11008 at M =
 // 16 / 64: 8.6 / 14.6 against 14.9 / 18.8; 4096x1024 at M = 16: 2.8 against
 // 7.4).  Up to 64 tokens on up to 12288 rows (22016x4096, a path asked for by
 // name, at M = 48 / 64: 37.9 / 39.6 against 28.6 / 29.9) while rows are not
@@ -255,7 +255,7 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 // K ranges: 1024 rows at K = 6144 / 8192 / 11008: 10.4, 11.0 / 12.3, 11.7 / 16.1,
 // 13.5; 2048 rows at K = 11008 / 13824: 16.7, 18.6 / 19.5, 20.6; 4096 rows at K =
 // 11008 / 16000: 17.4, 19.0 / 22.6, 21.1; 8192 rows at K = 4096 / 6144: 15.7, 16.2
-// / 20.3, 19.2).
+// / 20.3, 19.2, 11008 rows at K = 2048 / 4096: 14.9, 17.6 / 21.8, 20.0).
 // Above, each 64 tokens expand the weights again, which pays while the
 // grid is at most two workgroups per CU on rows of up to 8192 K, or one on
 // longer ones (4096x4096 at M = 128: 13.9 against 20.8, M = 256, four per CU,
@@ -269,7 +269,8 @@ hipError_t launch_ni(const Cfg& c, const SmallArgs& a, int64_t n_tiles, hipStrea
 // K = 16000 / 20480: 21.2, 22.7 / 26.3, 25.5).
 bool mx_small_wins(int64_t M, int64_t N, int64_t K) {
   if (M <= 32) return true;
-  if (M <= 64) return N <= 4096 ? K < 8192 || (K <= (M <= 48 ? 12288 : 14336) && N > 1536) : N <= 12288 && K <= 5120;
+  if (M <= 64) return N <= 4096 ? K < 8192 || (K <= (M <= 48 ? 12288 : 14336) && N > 1536)
+                             : N <= 12288 && K <= (N <= 8192 ? 5120 : 3072);
   const int64_t wgs = (N + kSmallRows - 1) / kSmallRows * ((M + 63) / 64);
   if (K <= 8192) return wgs <= 512;
   return wgs <= 256 && wgs >= (K <= 14336 ? 64 : K <= 16384 ? 160 : 256);

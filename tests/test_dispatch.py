@@ -67,7 +67,8 @@ INT8O, INT8S = sdq.Config.int_family(fmt_o="int8"), sdq.Config("int", 1, 8, "e4m
     (MX, 64, 1536, 11008, "mx_mfma 64 (18 K ranges)"), (MX, 64, 1568, 12288, "mx_small"),
     (MX, 48, 2048, 12320, "mx_mfma 64 (20 K ranges)"), (MX, 64, 2048, 14336, "mx_small"),
     (MX, 64, 2048, 14368, "mx_mfma 64 (23 K ranges)"), (MX, 64, 8192, 5120, "mx_small"),
-    (MX, 64, 8192, 5152, "mx_mfma 64 (7 K ranges)"), (MX, 128, 256, 11008, "mx_mfma 128 (18 K ranges)"),
+    (MX, 64, 8192, 5152, "mx_mfma 64 (7 K ranges)"), (MX, 64, 8224, 3072, "mx_small"),
+    (MX, 64, 11008, 4096, "mx_mfma 64 (5 K ranges)"), (MX, 128, 256, 11008, "mx_mfma 128 (18 K ranges)"),
     (MX, 128, 512, 11008, "mx_small"), (MX, 128, 1024, 16000, "mx_mfma 128 (25 K ranges)"),
     (MX, 192, 1024, 16000, "mx_small"), (MX, 128, 256, 8192, "mx_small"),
     # dual: the split-K form for few tokens on wide layers

@@ -60,7 +60,7 @@ def test_a_calls_own_workspace_outlives_another_stream(call, monkeypatch):
 
     say("own workspace on a side stream", call)
     with torch.cuda.stream(side):
-        torch.cuda._sleep(20_000_000)  # cycles; the call's kernels wait behind it
+        torch.cuda._sleep(100_000_000)  # cycles; the call's kernels wait behind it
     monkeypatch.setattr(torch, "empty", record)
     if call == "linear":
         sdq.linear(X, blob, N, K, INT, out=out, xq=q2, scales=s2, stream=side)
